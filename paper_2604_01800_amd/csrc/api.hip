@@ -108,6 +108,9 @@ PcgArgs make_pcg_args_at(const ppe_problem* p, const WsView& w, int nb, int R, i
   a.p1 = w.vec + 3 * N;
   a.partA = w.part;
   a.partB = w.part + (size_t)a.P * nb;
+  a.rzp = a.partB + a.P;
+  a.Prz = a.P;
+  a.rz_stride = 2 * a.P;
   a.partD = w.part + (size_t)3 * a.P * nb;
   a.e = w.vec + 4 * N;
   a.r1 = w.vec + 5 * N;
@@ -395,10 +398,12 @@ ppe_status attach_extras(ppe_problem* p, PcgArgs& a, int nb, const ppe_solve_opt
     a.jacobi = 0;
   }
   if (o.precond == PPE_PC_MG) {
-    ppe_status st = mg_ensure(p, o.mg_levels > 0 ? o.mg_levels : 4, nb, a.R, s);
+    ppe_status st = mg_ensure(p, o.mg_levels > 0 ? o.mg_levels : 4, nb, s);
     if (st != PPE_OK) return st;
     a.mg = p->mg;
     a.z = p->mg->z;
+    a.rzp = p->mg->rzpart;
+    a.Prz = a.rz_stride = mg_rz_parts(*p->mg, nb);
     a.jacobi = 0;
   }
   if (o.record_history) {

@@ -13,6 +13,8 @@ struct PcgArgs {
   float *xc, *r, *p0, *p1;  // [nb][N] each
   float* r1;                // [nb][N] second residual buffer (single-reduction iteration)
   double *partA, *partB;    // [nb][P], [nb][2][P]
+  const double* rzp;        // shares of r.z of a supplied z (Prz per solve, rz_stride apart): the
+  int Prz, rz_stride;       // second row of partB, or the V-cycle's own array
   double* part1;            // [2][nb][5][P] sums of the single-reduction iteration
   int P2;                   // workgroups per solve of the two-iteration form (56-column tiles)
   double* part2;            // [2][nb][11][P2] sums of the two-iteration form
@@ -75,7 +77,7 @@ void launch_hist_cg(const PcgArgs& a, int nb, int par, hipStream_t s);
 void launch_apply_multi(const Coef* coefs, int nx, int ny, int nb, const float* x, float* y, hipStream_t s);
 void launch_pcg_finish(const PcgArgs& a, int nb, hipStream_t s);
 // The multigrid V-cycle on the residual a.r into a.z (a.mg), ending with the
-// partial sums of r.z in the second half of a.partB.
+// shares of r.z in a.rzp.
 void launch_vcycle(const PcgArgs& a, int nb, hipStream_t s);
 
 }  // namespace ppe

@@ -23,13 +23,6 @@ void mg_free(MgData* m) {
 
 namespace {
 
-// Tile height of a coarse level's stencil kernels by its size.
-int level_rows(int64_t cells) {
-  if (cells >= ((int64_t)1 << 20)) return 8;
-  if (cells >= ((int64_t)1 << 17)) return 4;
-  return 2;
-}
-
 template <typename T>
 T* alloc_n(MgData* m, size_t n) {
   T* q = (T*)dev_alloc(sizeof(T) * (n ? n : 1));
@@ -50,10 +43,9 @@ void coarsen_axis(const std::vector<double>& h, const std::vector<double>& g, st
 
 }  // namespace
 
-ppe_status mg_ensure(ppe_problem* p, int L, int nb, int R0, hipStream_t s) {
+ppe_status mg_ensure(ppe_problem* p, int L, int nb, hipStream_t s) {
   MgData* m = p->mg;
-  // the fine level's tiling only matters when it writes the coarsest sums
-  if (m && m->L == L && m->nb >= nb && (L != 2 || m->R0 == R0)) return PPE_OK;
+  if (m && m->L == L && m->nb >= nb) return PPE_OK;
   mg_free(m);
   p->mg = nullptr;
   const int cnx = p->nx >> (L - 1), cny = p->ny >> (L - 1);
@@ -66,7 +58,6 @@ ppe_status mg_ensure(ppe_problem* p, int L, int nb, int R0, hipStream_t s) {
   m->uid = next_uid.fetch_add(1);
   m->L = L;
   m->nb = nb;
-  m->R0 = R0;
   m->lv.resize(L);
   auto fail = [&](const char* what) {
     mg_free(m);
@@ -85,7 +76,6 @@ ppe_status mg_ensure(ppe_problem* p, int L, int nb, int R0, hipStream_t s) {
     const int64_t N = (int64_t)v.nx * v.ny;
     if (l == 0) {
       v.c = p->coef;
-      v.R = R0;
     } else {
       // centres of merged cells (used by nothing in the V-cycle; kept consistent)
       std::vector<double> xcc(v.nx), ycc(v.ny);
@@ -100,14 +90,11 @@ ppe_status mg_ensure(ppe_problem* p, int L, int nb, int R0, hipStream_t s) {
         mg_free(m);
         return st;
       }
-      v.R = level_rows(N * nb);
       v.b = alloc_n<float>(m, (size_t)N * nb);
       v.x = alloc_n<float>(m, (size_t)N * nb);
       v.y = alloc_n<float>(m, (size_t)N * nb);
-      v.d = alloc_n<float>(m, (size_t)N * nb);
-      if (!v.b || !v.x || !v.y || !v.d) return fail("level buffers");
+      if (!v.b || !v.x || !v.y) return fail("level buffers");
     }
-    v.P = (int)stencil_grid(v.c, v.R, 1).x;
     if (l + 1 < L) {
       std::vector<double> hc, gc;
       coarsen_axis(hx, gx, hc, gc);
@@ -120,9 +107,9 @@ ppe_status mg_ensure(ppe_problem* p, int L, int nb, int R0, hipStream_t s) {
   }
   const int64_t N0 = (int64_t)p->nx * p->ny;
   m->z = alloc_n<float>(m, (size_t)N0 * nb);
-  m->d0 = alloc_n<float>(m, (size_t)N0 * nb);
-  m->y0 = alloc_n<float>(m, (size_t)N0 * nb);
-  if (!m->z || !m->d0 || !m->y0) return fail("fine-level buffers");
+  m->x0 = alloc_n<float>(m, (size_t)N0 * nb);
+  m->rzpart = alloc_n<double>(m, (size_t)mg_max_parts(m->lv[0]) * nb);
+  if (!m->z || !m->x0 || !m->rzpart) return fail("fine-level buffers");
 
   // Coarsest level: hx, gx, hy, gy now hold its arrays.
   const int nxc = (int)hx.size(), nyc = (int)hy.size();
@@ -166,8 +153,7 @@ ppe_status mg_ensure(ppe_problem* p, int L, int nb, int R0, hipStream_t s) {
   m->psiT = alloc_n<double>(m, psiT.size());
   m->dinv = alloc_n<double>(m, dinv.size());
   m->bh = alloc_n<double>(m, (size_t)nxc * nyc * nb);
-  m->bP = L >= 2 ? m->lv[L - 2].P : 1;
-  m->bpart = alloc_n<double>(m, (size_t)m->bP * nb);
+  m->bpart = alloc_n<double>(m, (L >= 2 ? (size_t)mg_max_parts(m->lv[L - 2]) : 1) * nb);
   m->xpart = alloc_n<double>(m, (size_t)nyc * nb);
   if (!m->phi || !m->phiT || !m->psi || !m->psiT || !m->dinv || !m->bh || !m->bpart || !m->xpart)
     return fail("coarsest-level buffers");

@@ -20,19 +20,17 @@ constexpr int kMgCoarseMaxNy = 2048;
 // side is the PCG residual and its output the preconditioned residual z.
 struct MgLevel {
   int nx = 0, ny = 0;
-  int R = 2, P = 0;           // tile rows per wavefront and workgroups per solve
   Coef c{};                   // operator coefficients (level 0: the problem's)
   void* dev_coef = nullptr;   // coefficient block owned by levels >= 1
   float* b = nullptr;         // [nb][N] right-hand side (levels >= 1)
-  float* x = nullptr;         // [nb][N] approximate solution (levels >= 1)
-  float* y = nullptr;         // [nb][N] x after the first post-smoothing step (levels >= 1): the
-                              // post-smoothing kernels read x on a halo, so they never write in place
-  float* d = nullptr;         // [nb][N] Chebyshev direction of the post-smoothing
+  float* x = nullptr;         // [nb][N] x after the pre-smoothing; the coarsest level's solution (levels >= 1)
+  float* y = nullptr;         // [nb][N] x after the post-smoothing (levels >= 1): it reads x on a halo,
+                              // so it never writes in place
 };
 
 struct MgData {
   uint64_t uid = 0;  // process-unique build id (cached graphs key on it, not on the address)
-  int L = 0, nb = 0, R0 = 0;
+  int L = 0, nb = 0;
   std::vector<MgLevel> lv;
   // Coarsest level: A_c = T_x (x) H_y + H_x (x) T_y is diagonalised by the
   // generalised eigenvectors of both axes, T_x phi = lam H_x phi
@@ -47,18 +45,20 @@ struct MgData {
   double* psiT = nullptr;  // [nyc][nyc] psiT[j][j'] = psi[j'][j]
   double* dinv = nullptr;  // [nyc][nxc] 1 / (lam_k + mu_j), 0 for the constant mode
   double* bh = nullptr;    // [nb][nyc][nxc] transformed right-hand side, then the mode solutions
-  double* bpart = nullptr; // [nb][bP] partial sums of the coarsest right-hand side
-  int bP = 0;
+  double* bpart = nullptr; // [nb][workgroups of level L-2] partial sums of the coarsest right-hand side
   double* xpart = nullptr; // [nb][nyc] row sums of the coarsest solution
   float* z = nullptr;      // [nb][N0] output of the V-cycle on the fine level
-  float* d0 = nullptr;     // [nb][N0] post-smoothing direction on the fine level
-  float* y0 = nullptr;     // [nb][N0] fine-level x after the first post-smoothing step
+  float* x0 = nullptr;     // [nb][N0] fine-level x after the pre-smoothing
+  double* rzpart = nullptr;  // [nb][mg_max_parts] workgroup shares of r.z
   std::vector<void*> owned;
 };
 
-// Builds (or reuses) the hierarchy of L levels for nb right-hand sides, with
-// the fine level tiled at R0 rows per wavefront.
-ppe_status mg_ensure(ppe_problem* p, int L, int nb, int R0, hipStream_t s);
+// Shares of r.z that a V-cycle over nb right-hand sides leaves per solve.
+int mg_rz_parts(const MgData& m, int nb);
+// The most workgroups per solve that a level's kernels run (their smallest tiles).
+int mg_max_parts(const MgLevel& v);
+// Builds (or reuses) the hierarchy of L levels for nb right-hand sides.
+ppe_status mg_ensure(ppe_problem* p, int L, int nb, hipStream_t s);
 void mg_free(MgData* m);
 
 }  // namespace ppe

@@ -15,18 +15,21 @@
 //          r4 = b - A x4;  x5 = x4 + c1 d + c2 D^-1 r4
 // with theta, delta the interval's centre and half-width, c1 = rho1 rho0,
 // c2 = 2 rho1 / delta (rho0 = delta / theta, rho1 = 1 / (2 theta/delta - rho0)).
-// Each kernel recomputes what it needs on a one-cell halo, so a level costs
-// four launches: pre-smoothing, residual + restriction, prolongation + first
-// post step, second post step. A kernel that reads a vector on a halo never
-// writes that vector (other workgroups may still be reading it): x2 and x5
-// live in x, x4 in y. The coarsest level is solved exactly by the
-// separable direct method (transforms to the eigenbases of both axes, a
-// diagonal scaling, and back) in FP64, with the right-hand side's mean removed
-// before and the solution's mean after, i.e. the minimum-norm solution.
+// A level costs two launches: down (pre-smoothing, residual, restriction) and
+// up (prolongation, both post steps). Each takes two stencil applications on a
+// tile with a two-cell halo, recomputed instead of exchanged: the cycle is bound by the
+// latency of its dependent launches (2.6 to 5 us each at 128^2 to 1024^2, for
+// at most 4 MB a vector), not by the bytes or the arithmetic that the wider halo adds. A
+// kernel that reads a vector on a halo never writes that vector (other
+// workgroups may still be reading it): x2 lives in x, x5 in y. The coarsest
+// level is solved exactly by the separable direct method (transforms to the
+// eigenbases of both axes, a diagonal scaling, and back) in FP64, with the
+// right-hand side's mean removed before and the solution's mean after, i.e. the
+// minimum-norm solution.
 //
 // Vectors are FP32; every kernel returns at once for a solve whose done flag
-// is set. The last kernel of the fine level leaves the partial sums of r.z in
-// the PCG's partial-sum array, tiled as its phase kernels are.
+// is set. The last kernel of the fine level leaves its workgroups' shares of
+// r.z, which phase A of the PCG adds up.
 #include <hip/hip_runtime.h>
 
 #include "common.hpp"
@@ -54,9 +57,8 @@ struct LevelArgs {
   Coef c;
   int64_t N;               // cells per solve on this level
   const float* b;          // [nb][N]
-  float* x;                // [nb][N] x2, then x5
-  float* y;                // [nb][N] x4
-  float* d;                // [nb][N]
+  float* x;                // [nb][N] x2
+  float* y;                // [nb][N] x5
   const int32_t* flags;    // [nb] done codes of the solves
   Cheb k;
   // restriction target / coarse correction source (level l+1)
@@ -68,7 +70,7 @@ struct LevelArgs {
   double* bpart;           // [nb][P] partial sums of the coarse right-hand side (coarsest only)
   const double* xpart;     // [nb][nyc] row sums of the coarsest solution (coarsest only)
   int nyc;
-  double* rzpart;          // fine level: partial sums of r.z, PCG layout (stride 2 P per solve), else NULL
+  double* rzpart;          // fine level: [nb][P] shares of r.z, else NULL
   int P;                   // workgroups per solve of this level
 };
 
@@ -78,79 +80,116 @@ __device__ __forceinline__ float dinv_at(float hyj, float gs, float gn, float hx
   return 1.0f / fmaxf(diag_of(hyj, gs, gn, hx, gw, ge), 1e-30f);
 }
 
-// Pre-smoothing from a zero guess: writes x2.
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_mg_pre(LevelArgs a) {
-  const int s = blockIdx.z, nx = a.c.nx, ny = a.c.ny;
-  if (a.flags[s] != DONE_NO) return;
-  const size_t off = (size_t)s * a.N;
-  const uint64_t vbytes = (uint64_t)a.N * 4;
-  const TileXY tl = tile_xy(nx, ny, R);
-  const ColIdx ci = col_idx(nx, tl);
-  const int j0 = tl.j0;
-  Tile<float, R> tb;
-  load_tile<R>(make_rsrc(a.b + off, vbytes), nx, ny, j0, ci, tb);
-  RowCoef<float, R> rc;
-  load_rows<float, R>(a.c.hy, a.c.gy, j0, rc);
-  const ColCoef<float> k = load_cols<float>(a.c.hx, a.c.gx, ci);
-  Tile<float, R> x1;
-  float dv[R];
-#pragma unroll
-  for (int q = 0; q < R + 2; ++q) {
-    const float di = dinv_at(rc.hy[q], rc.gy[q], rc.gy[q + 1], k.hx, k.gw, k.ge);
-    x1.own[q] = tb.own[q] * di * a.k.inv_theta;
-    if (q >= 1 && q <= R) dv[q - 1] = di;
-  }
-#pragma unroll
-  for (int q = 0; q < R; ++q)
-    x1.halo[q] = tb.halo[q] * dinv_at(rc.hy[q + 1], rc.gy[q + 1], rc.gy[q + 2], k.hxh, k.gwh, k.geh) * a.k.inv_theta;
-  float Ax[R];
-  stencil_rows<float, R>(x1, rc, k, Ax);
-  const auto xs = make_rsrc(a.x + off, vbytes);
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const float r1 = tb.own[q + 1] - Ax[q];
-    const float x2 = x1.own[q + 1] + a.k.c1 * x1.own[q + 1] + a.k.c2 * dv[q] * r1;
-    bstore(xs, cell_off(ci.ok, j0 + q, ny, nx, ci.i), x2);
-  }
+// Tiles of the level kernels: a wavefront's 64 lanes hold 60 owned columns and
+// two halo columns on either side (east and west neighbours are DPP wave
+// shifts; a stencil application loses one lane at each end), and R owned rows
+// between two halo rows above and below. Tiles start on even columns and
+// rows, so a 2 x 2 block of children never crosses a tile. XCD banded as the
+// 64-column tiles are.
+constexpr int kMgH = 2;
+constexpr int kMgOwn = kWave - 2 * kMgH;
+
+__device__ __forceinline__ TileXY mg_tile_xy(int nx, int ny, int R) {
+  const int gxt = (nx + kMgOwn - 1) / kMgOwn;
+  const int gyt = (ny + kWaves * R - 1) / (kWaves * R);
+  const int T = gxt * gyt;
+  const int per = (T + 7) / 8;
+  int t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  TileXY o;
+  o.valid = t < T;
+  if (!o.valid) t = 0;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  o.i0 = (t % gxt) * kMgOwn - kMgH;
+  o.j0 = ((t / gxt) * kWaves + w) * R;
+  return o;
 }
 
-// Residual of x2 and its restriction (sum over 2 x 2 children) to the coarse
-// right-hand side; on the way to the coarsest level also the partial sums of
-// the coarse right-hand side (its mean is removed there).
+// Rows per wavefront of a level: enough workgroups to cover the chip.
+static int mg_rows(int64_t cells) {
+  if (cells >= ((int64_t)1 << 20)) return 8;
+  if (cells >= ((int64_t)1 << 17)) return 4;
+  return 2;
+}
+
+static int mg_tiles(int nx, int ny, int R) {
+  const int T = ((nx + kMgOwn - 1) / kMgOwn) * ((ny + kWaves * R - 1) / (kWaves * R));
+  return 8 * ((T + 7) / 8);
+}
+
+// This lane's column of a level tile and the row coefficients of its R + 4
+// rows (row q is j0 - 2 + q; the padded arrays read 0 off the grid).
 template <int R>
-__global__ __launch_bounds__(kBlock) void k_mg_restrict(LevelArgs a) {
+struct MgTile {
+  int i, j0;
+  bool inx, own;
+  float hx, gw, ge;
+  float hy[R + 2 * kMgH], gy[R + 2 * kMgH + 1];
+
+  __device__ __forceinline__ MgTile(const Coef& c) {
+    const TileXY tl = mg_tile_xy(c.nx, c.ny, R);
+    const int lane = threadIdx.x & (kWave - 1);
+    i = tl.i0 + lane;
+    j0 = tl.j0;
+    inx = tl.valid && i >= 0 && i < c.nx;
+    own = inx && lane >= kMgH && lane < kWave - kMgH;
+#pragma unroll
+    for (int q = 0; q < R + 2 * kMgH; ++q) hy[q] = c.hy[j0 - kMgH + q];
+#pragma unroll
+    for (int q = 0; q < R + 2 * kMgH + 1; ++q) gy[q] = c.gy[j0 - kMgH + q];
+    hx = c.hx[i];
+    gw = c.gx[i];
+    ge = c.gx[i + 1];
+  }
+  __device__ __forceinline__ float dinv(int q) const { return dinv_at(hy[q], gy[q], gy[q + 1], hx, gw, ge); }
+  // (A v) on row q of a column of R + 4 values; lanes 0 and 63 lack a neighbour
+  __device__ __forceinline__ float apply(const float (&v)[R + 2 * kMgH], int q) const {
+    const float ve = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v[q]), 0x130, 0xf, 0xf, true));
+    const float vw = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v[q]), 0x138, 0xf, 0xf, true));
+    return stencil5(v[q], ve, vw, v[q + 1], v[q - 1], hy[q], gy[q], gy[q + 1], hx, gw, ge);
+  }
+};
+
+// Down: pre-smoothing from a zero guess (x2, stored), its residual and the
+// restriction of that (sum over 2 x 2 children) to the coarse right-hand side;
+// on the way to the coarsest level also the partial sums of the coarse
+// right-hand side (its mean is removed there). Bytes per cell: b read, x2
+// written, a quarter of a coarse value written (9 B). At 1024^2 one launch of
+// 5.2 us replaces two of 4.7 and 3.3 us.
+template <int R>
+__global__ __launch_bounds__(kBlock) void k_mg_down(LevelArgs a) {
+  constexpr int Q = R + 2 * kMgH;
   __shared__ double lds[kWaves];
   const int s = blockIdx.z, nx = a.c.nx, ny = a.c.ny;
   if (a.flags[s] != DONE_NO) return;
   const size_t off = (size_t)s * a.N;
   const uint64_t vbytes = (uint64_t)a.N * 4;
-  const TileXY tl = tile_xy(nx, ny, R);
-  const ColIdx ci = col_idx(nx, tl);
-  const int j0 = tl.j0;
-  Tile<float, R> tx;
-  float bv[R];
-  load_tile<R>(make_rsrc(a.x + off, vbytes), nx, ny, j0, ci, tx);
-  load_rows_own<R>(make_rsrc(a.b + off, vbytes), nx, ny, j0, ci, bv);
-  RowCoef<float, R> rc;
-  load_rows<float, R>(a.c.hy, a.c.gy, j0, rc);
-  const ColCoef<float> k = load_cols<float>(a.c.hx, a.c.gx, ci);
-  float Ax[R];
-  stencil_rows<float, R>(tx, rc, k, Ax);
+  const MgTile<R> t(a.c);
+  const auto bs = make_rsrc(a.b + off, vbytes);
+  float b[Q], x1[Q], x2[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) b[q] = bload(bs, cell_off(t.inx, t.j0 - kMgH + q, ny, nx, t.i));
+#pragma unroll
+  for (int q = 0; q < Q; ++q) x1[q] = b[q] * t.dinv(q) * a.k.inv_theta;
+  x2[0] = x2[Q - 1] = 0.f;
+  const auto xs = make_rsrc(a.x + off, vbytes);
+#pragma unroll
+  for (int q = 1; q < Q - 1; ++q) {
+    const float r1 = b[q] - t.apply(x1, q);
+    x2[q] = x1[q] + a.k.c1 * x1[q] + a.k.c2 * t.dinv(q) * r1;
+    if (q >= kMgH && q < kMgH + R) bstore(xs, cell_off(t.own, t.j0 - kMgH + q, ny, nx, t.i), x2[q]);
+  }
   const int lane = threadIdx.x & (kWave - 1);
   const auto cs = make_rsrc(a.bc + (size_t)s * a.Nc, (uint64_t)a.Nc * 4);
   double acc = 0.0;
 #pragma unroll
-  for (int q = 0; q < R; q += 2) {
-    // rows j0+q and j0+q+1 form one coarse row (j0 and R are even); off the
-    // grid both the residual's inputs and its coefficients are 0
-    const float v = (bv[q] - Ax[q]) + (bv[q + 1] - Ax[q + 1]);
-    float ve, vw;
-    east_west(v, 0.f, ve, vw);
-    const float sum = v + ve;  // columns i and i+1 (i even; the pair never crosses a 64-column strip)
-    const int j = j0 + q;
-    const bool w = ci.ok && (lane & 1) == 0 && j < ny;
-    bstore(cs, w ? (uint32_t)((j >> 1) * a.nxc + (ci.i >> 1)) * 4u : kOOB, sum);
+  for (int q = kMgH; q < kMgH + R; q += 2) {
+    // rows j and j + 1 form one coarse row (j0 and R are even); off the grid
+    // both the residual's inputs and its coefficients are 0
+    const float v = (b[q] - t.apply(x2, q)) + (b[q + 1] - t.apply(x2, q + 1));
+    const float sum = v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
+    const int j = t.j0 - kMgH + q;
+    const bool w = t.own && (lane & 1) == 0 && j < ny;
+    bstore(cs, w ? (uint32_t)((j >> 1) * a.nxc + (t.i >> 1)) * 4u : kOOB, sum);
     if (w) acc += (double)sum;
   }
   if (a.coarsest) {
@@ -159,108 +198,64 @@ __global__ __launch_bounds__(kBlock) void k_mg_restrict(LevelArgs a) {
   }
 }
 
-// Coarse correction and the first post-smoothing step: x3 = x2 + P e,
-// d = D^-1 (b - A x3) / theta, x4 = x3 + d; reads x2 from x, writes x4 to y
-// and d.
+// Up: coarse correction x3 = x2 + P e and both post-smoothing steps,
+//   d = D^-1 (b - A x3) / theta, x4 = x3 + d, x5 = x4 + c1 d + c2 D^-1 (b - A x4);
+// reads x2 from x, writes x5 to y. On the fine level b is the PCG residual r
+// and x5 is z; the workgroup's share of r.z goes to rzpart. Bytes per cell:
+// x2 and b read, a quarter of a coarse value read, x5 written (13 B). At
+// 1024^2 one launch of 6.2 us replaces two of 5.2 and 4.8 us.
 template <int R>
-__global__ __launch_bounds__(kBlock) void k_mg_post1(LevelArgs a) {
+__global__ __launch_bounds__(kBlock) void k_mg_up(LevelArgs a) {
+  constexpr int Q = R + 2 * kMgH;
   __shared__ double lds[kWaves];
   const int s = blockIdx.z, nx = a.c.nx, ny = a.c.ny;
   if (a.flags[s] != DONE_NO) return;
   const size_t off = (size_t)s * a.N;
   const uint64_t vbytes = (uint64_t)a.N * 4;
-  const TileXY tl = tile_xy(nx, ny, R);
-  const ColIdx ci = col_idx(nx, tl);
-  const int j0 = tl.j0;
-  Tile<float, R> tx;
-  float bv[R];
-  load_tile<R>(make_rsrc(a.x + off, vbytes), nx, ny, j0, ci, tx);
-  load_rows_own<R>(make_rsrc(a.b + off, vbytes), nx, ny, j0, ci, bv);
-  // coarse values of the parents of the tile's cells (0 off the grid)
+  const MgTile<R> t(a.c);
+  const auto xs = make_rsrc(a.x + off, vbytes), bs = make_rsrc(a.b + off, vbytes);
   const auto es = make_rsrc(a.ec + (size_t)s * a.Nc, (uint64_t)a.Nc * 4);
-  Tile<float, R> te;
+  float x3[Q], x4[Q], b[Q], d[R], e[Q / 2];
 #pragma unroll
-  for (int q = 0; q < R + 2; ++q) {
-    const int j = j0 - 1 + q;
-    te.own[q] = bload(es, (ci.ok && j >= 0 && j < ny) ? (uint32_t)((j >> 1) * a.nxc + (ci.i >> 1)) * 4u : kOOB);
+  for (int q = 0; q < Q; ++q) x3[q] = bload(xs, cell_off(t.inx, t.j0 - kMgH + q, ny, nx, t.i));
+#pragma unroll
+  for (int h = 0; h < Q / 2; ++h) {  // the parents of rows 2h and 2h + 1 (0 off the grid)
+    const int j = t.j0 - kMgH + 2 * h;
+    e[h] = bload(es, (t.inx && j >= 0 && j < ny) ? (uint32_t)((j >> 1) * a.nxc + (t.i >> 1)) * 4u : kOOB);
   }
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int j = j0 + q;
-    te.halo[q] = bload(es, (ci.hok && j < ny) ? (uint32_t)((j >> 1) * a.nxc + (ci.ih >> 1)) * 4u : kOOB);
-  }
-  RowCoef<float, R> rc;
-  load_rows<float, R>(a.c.hy, a.c.gy, j0, rc);
-  const ColCoef<float> k = load_cols<float>(a.c.hx, a.c.gx, ci);
+  for (int q = 1; q < Q - 1; ++q) b[q] = bload(bs, cell_off(t.inx, t.j0 - kMgH + q, ny, nx, t.i));
   float emean = 0.f;
   if (a.coarsest) {
     // minimum-norm coarsest solution: subtract its plain mean (fixed-order sum)
     double sum = 0.0;
-    for (int t = threadIdx.x; t < a.nyc; t += kBlock) sum += a.xpart[(size_t)s * a.nyc + t];
+    for (int u = threadIdx.x; u < a.nyc; u += kBlock) sum += a.xpart[(size_t)s * a.nyc + u];
     emean = (float)(block_sum(sum, lds) / (double)a.Nc);
   }
-  Tile<float, R> x3;
 #pragma unroll
-  for (int q = 0; q < R + 2; ++q) {
-    const int j = j0 - 1 + q;
-    const bool in = ci.ok && j >= 0 && j < ny;
-    x3.own[q] = tx.own[q] + (in ? te.own[q] - emean : 0.f);
+  for (int q = 0; q < Q; ++q) {
+    const int j = t.j0 - kMgH + q;
+    x3[q] += (t.inx && j >= 0 && j < ny) ? e[q / 2] - emean : 0.f;
   }
+  x4[0] = x4[Q - 1] = 0.f;
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const bool in = ci.hok && j0 + q < ny;
-    x3.halo[q] = tx.halo[q] + (in ? te.halo[q] - emean : 0.f);
+  for (int q = 1; q < Q - 1; ++q) {
+    const float dd = (b[q] - t.apply(x3, q)) * t.dinv(q) * a.k.inv_theta;
+    x4[q] = x3[q] + dd;
+    if (q >= kMgH && q < kMgH + R) d[q - kMgH] = dd;
   }
-  float Ax[R];
-  stencil_rows<float, R>(x3, rc, k, Ax);
-  const auto xs = make_rsrc(a.y + off, vbytes);
-  const auto ds = make_rsrc(a.d + off, vbytes);
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const float di = dinv_at(rc.hy[q + 1], rc.gy[q + 1], rc.gy[q + 2], k.hx, k.gw, k.ge);
-    const float dd = (bv[q] - Ax[q]) * di * a.k.inv_theta;
-    const uint32_t o = cell_off(ci.ok, j0 + q, ny, nx, ci.i);
-    bstore(xs, o, x3.own[q + 1] + dd);
-    bstore(ds, o, dd);
-  }
-}
-
-// Second post-smoothing step: x5 = x4 + c1 d + c2 D^-1 (b - A x4); reads x4
-// from y, writes x5 to x. On the fine level b is the PCG residual r and x5
-// is z; the workgroup's share of r.z goes to the PCG's partial sums.
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_mg_post2(LevelArgs a) {
-  __shared__ double lds[kWaves];
-  const int s = blockIdx.z, nx = a.c.nx, ny = a.c.ny;
-  if (a.flags[s] != DONE_NO) return;
-  const size_t off = (size_t)s * a.N;
-  const uint64_t vbytes = (uint64_t)a.N * 4;
-  const TileXY tl = tile_xy(nx, ny, R);
-  const ColIdx ci = col_idx(nx, tl);
-  const int j0 = tl.j0;
-  Tile<float, R> tx;
-  float bv[R], dv[R];
-  load_tile<R>(make_rsrc(a.y + off, vbytes), nx, ny, j0, ci, tx);
-  load_rows_own<R>(make_rsrc(a.b + off, vbytes), nx, ny, j0, ci, bv);
-  load_rows_own<R>(make_rsrc(a.d + off, vbytes), nx, ny, j0, ci, dv);
-  RowCoef<float, R> rc;
-  load_rows<float, R>(a.c.hy, a.c.gy, j0, rc);
-  const ColCoef<float> k = load_cols<float>(a.c.hx, a.c.gx, ci);
-  float Ax[R];
-  stencil_rows<float, R>(tx, rc, k, Ax);
-  const auto xs = make_rsrc(a.x + off, vbytes);
+  const auto ys = make_rsrc(a.y + off, vbytes);
   double rz = 0.0;
 #pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const float di = dinv_at(rc.hy[q + 1], rc.gy[q + 1], rc.gy[q + 2], k.hx, k.gw, k.ge);
-    const float x5 = tx.own[q + 1] + a.k.c1 * dv[q] + a.k.c2 * di * (bv[q] - Ax[q]);
-    const uint32_t o = cell_off(ci.ok, j0 + q, ny, nx, ci.i);
-    bstore(xs, o, x5);
-    if (o != kOOB) rz += (double)bv[q] * (double)x5;
+  for (int q = kMgH; q < kMgH + R; ++q) {
+    const float x5 = x4[q] + a.k.c1 * d[q - kMgH] + a.k.c2 * t.dinv(q) * (b[q] - t.apply(x4, q));
+    const uint32_t o = cell_off(t.own, t.j0 - kMgH + q, ny, nx, t.i);
+    bstore(ys, o, x5);
+    if (o != kOOB) rz += (double)b[q] * (double)x5;
   }
   if (a.rzpart) {
     rz = block_sum(rz, lds);
-    if (threadIdx.x == 0) a.rzpart[(size_t)s * 2 * a.P + block_linear()] = rz;
+    if (threadIdx.x == 0) a.rzpart[(size_t)s * a.P + block_linear()] = rz;
   }
 }
 
@@ -282,7 +277,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_rz(LevelArgs a) {
 #pragma unroll
   for (int q = 0; q < R; ++q) rz += (double)bv[q] * (double)xv[q];
   rz = block_sum(rz, lds);
-  if (threadIdx.x == 0) a.rzpart[(size_t)s * 2 * a.P + block_linear()] = rz;
+  if (threadIdx.x == 0) a.rzpart[(size_t)s * a.P + block_linear()] = rz;
 }
 
 namespace {
@@ -391,23 +386,22 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
   const MgData& m = *pa.mg;
   const int L = m.L;
   const Cheb k = cheb_consts();
+  auto rows = [&](int l) { return mg_rows((int64_t)m.lv[l].nx * m.lv[l].ny * nb); };
   // level l's arguments; the fine level reads the PCG residual and writes z
-  // with the PCG's tiling, so its r.z partials line up with phase A's sums
   auto level = [&](int l) {
     const MgLevel& v = m.lv[l];
     LevelArgs a{};
     a.c = v.c;
     a.N = (int64_t)v.nx * v.ny;
     a.b = l == 0 ? pa.r : v.b;
-    a.x = l == 0 ? m.z : v.x;
-    a.y = l == 0 ? m.y0 : v.y;
-    a.d = l == 0 ? m.d0 : v.d;
+    a.x = l == 0 ? m.x0 : v.x;
+    a.y = l == 0 ? m.z : v.y;
     a.flags = pa.flags;
     a.k = k;
     if (l + 1 < L) {
       const MgLevel& c = m.lv[l + 1];
       a.bc = c.b;
-      a.ec = c.x;
+      a.ec = l + 1 == L - 1 ? c.x : c.y;
       a.nxc = c.nx;
       a.Nc = (int64_t)c.nx * c.ny;
       a.coarsest = l + 1 == L - 1;
@@ -415,15 +409,13 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
       a.xpart = m.xpart;
       a.nyc = c.ny;
     }
-    a.P = l == 0 ? pa.P : v.P;
-    a.rzpart = l == 0 ? pa.partB + pa.P : nullptr;
+    a.P = mg_tiles(v.nx, v.ny, rows(l));
+    a.rzpart = l == 0 ? m.rzpart : nullptr;
     return a;
   };
-  auto rows = [&](int l) { return l == 0 ? pa.R : m.lv[l].R; };
   for (int l = 0; l + 1 < L; ++l) {
     const LevelArgs a = level(l);
-    const dim3 g = stencil_grid(a.c, rows(l), nb);
-    PPE_MG_DISPATCH(rows(l), k_mg_pre<RR><<<g, kBlock, 0, s>>>(a); k_mg_restrict<RR><<<g, kBlock, 0, s>>>(a));
+    PPE_MG_DISPATCH(rows(l), k_mg_down<RR><<<dim3(a.P, 1, nb), kBlock, 0, s>>>(a));
   }
   {
     const MgLevel& c = m.lv[L - 1];
@@ -440,7 +432,7 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
     ca.dinv = m.dinv;
     ca.bh = m.bh;
     ca.bpart = L == 1 ? nullptr : m.bpart;
-    ca.bP = m.bP;
+    ca.bP = L == 1 ? 1 : mg_tiles(m.lv[L - 2].nx, m.lv[L - 2].ny, rows(L - 2));
     ca.xpart = m.xpart;
     ca.flags = pa.flags;
     const size_t shm = sizeof(double) * m.nxc;
@@ -449,16 +441,25 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
     k_mg_cbwd<<<dim3(m.nyc, 1, nb), kBlock, shm, s>>>(ca);
   }
   if (L == 1) {
-    const LevelArgs a = level(0);
-    const dim3 g = stencil_grid(a.c, pa.R, nb);
-    PPE_MG_DISPATCH(pa.R, k_mg_rz<RR><<<g, kBlock, 0, s>>>(a));
+    LevelArgs a = level(0);
+    a.x = m.z;
+    const dim3 g = stencil_grid(a.c, rows(0), nb);
+    a.P = (int)g.x;
+    PPE_MG_DISPATCH(rows(0), k_mg_rz<RR><<<g, kBlock, 0, s>>>(a));
     return;
   }
   for (int l = L - 2; l >= 0; --l) {
     const LevelArgs a = level(l);
-    const dim3 g = stencil_grid(a.c, rows(l), nb);
-    PPE_MG_DISPATCH(rows(l), k_mg_post1<RR><<<g, kBlock, 0, s>>>(a); k_mg_post2<RR><<<g, kBlock, 0, s>>>(a));
+    PPE_MG_DISPATCH(rows(l), k_mg_up<RR><<<dim3(a.P, 1, nb), kBlock, 0, s>>>(a));
   }
 }
+
+int mg_rz_parts(const MgData& m, int nb) {
+  const MgLevel& v = m.lv[0];
+  const int R = mg_rows((int64_t)v.nx * v.ny * nb);
+  return m.L == 1 ? (int)stencil_grid(v.c, R, 1).x : mg_tiles(v.nx, v.ny, R);
+}
+
+int mg_max_parts(const MgLevel& v) { return mg_tiles(v.nx, v.ny, 2); }
 
 }  // namespace ppe

@@ -347,7 +347,8 @@ __global__ __launch_bounds__(kBlock) void k_pcg_a(PcgArgs a, int par, int force,
   // above are already in flight whichever way the test goes.
   const double* pb = a.partB + (size_t)s * 2 * P;
   const double rr = reduce_partials(pb, P, lds);
-  const double rz = reduce_partials(pb + P, P, lds);
+  const double rz = PB == 2 ? reduce_partials(a.rzp + (size_t)s * a.rz_stride, a.Prz, lds)
+                            : reduce_partials(pb + P, P, lds);
   if (dprev) {
     if (leader) st->dflag[par] = dprev;
     return;
