@@ -66,6 +66,7 @@ struct LevelArgs {
   const float* ec;         // [nb][Nc] coarse solution
   int nxc;
   int64_t Nc;
+  int bc_t;                // bc is stored transposed ([nxc][nyc])
   int coarsest;            // level l+1 is the coarsest: means are taken there
   double* bpart;           // [nb][P] partial sums of the coarse right-hand side (coarsest only)
   const double* xpart;     // [nb][nyc] row sums of the coarsest solution (coarsest only)
@@ -189,7 +190,8 @@ __global__ __launch_bounds__(kBlock) void k_mg_down(LevelArgs a) {
     const float sum = v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
     const int j = t.j0 - kMgH + q;
     const bool w = t.own && (lane & 1) == 0 && j < ny;
-    bstore(cs, w ? (uint32_t)((j >> 1) * a.nxc + (t.i >> 1)) * 4u : kOOB, sum);
+    const int jc = j >> 1, ic = t.i >> 1;
+    bstore(cs, w ? (uint32_t)(a.bc_t ? ic * (ny >> 1) + jc : jc * a.nxc + ic) * 4u : kOOB, sum);
     if (w) acc += (double)sum;
   }
   if (a.coarsest) {
@@ -373,6 +375,105 @@ __global__ __launch_bounds__(kBlock) void k_mg_cbwd(CoarseArgs a) {
   if (threadIdx.x == 0) a.xpart[(size_t)s * a.nyc + j] = sum;
 }
 
+// The coarsest solve for axes of at most kMgSmall cells (a 1024 x 1024 grid at
+// four levels has 128 x 128): two launches in place of the three above. What
+// bounds it is the latency of its chain of dense transforms, so every matrix
+// value is loaded before the first product needs one: thread (j, part) keeps the
+// rows [32 part, 32 part + 32) of each transform's column j in registers, the
+// four parts of a sum meet in LDS, and only LDS traffic is left between the
+// transforms. The three launches waited on the L2 four times per transform
+// with half of their threads idle: 19.1 us at 128 x 128, against 8.1 + 6.0 us here.
+// (On FP64 matrix cores, 16 modes per workgroup, the same work took 39 us: eight
+// compute units then load all of the matrices.)
+constexpr int kMgSmall = 128;
+constexpr int kMgParts = 4;
+constexpr int kMgPer = kMgSmall / kMgParts;  // matrix rows per thread
+constexpr int kMgCB = kMgSmall * kMgParts;   // threads of a workgroup
+
+// Rows q0 .. q0 + 31 of column j of the n x n matrix M (0 outside).
+__device__ __forceinline__ void mg_load_col(const double* __restrict__ M, int n, int j, int q0, double (&v)[kMgPer]) {
+  const auto rs = make_rsrc(M, (uint64_t)n * n * 8);
+#pragma unroll
+  for (int u = 0; u < kMgPer; ++u)
+    v[u] = bload64(rs, (j < n && q0 + u < n) ? (uint32_t)((q0 + u) * n + j) * 8u : kOOB);
+}
+
+// sum over the parts of sum_u m[u] x[q0 + u] (x in LDS, zero past n), for the
+// column of this thread; every thread of the column gets the same bits.
+__device__ __forceinline__ double mg_dot_parts(const double (&m)[kMgPer], const double* x, int q0, double* red) {
+  double acc = 0.0;
+#pragma unroll
+  for (int u = 0; u < kMgPer; ++u) acc += m[u] * x[q0 + u];
+  __syncthreads();  // the reads of red before this sum are done
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  const int j = threadIdx.x & (kMgSmall - 1);
+  return ((red[j] + red[kMgSmall + j]) + red[2 * kMgSmall + j]) + red[3 * kMgSmall + j];
+}
+
+// Mode k of all rows (one workgroup per mode): bh[j][k] = the solution's
+// coefficients in the eigenbasis of x, psi diag(1 / (lam_k + mu_j)) psi^T
+// (b - mean) phi, with b transposed ([nxc][nyc], as k_mg_down leaves it).
+__global__ __launch_bounds__(kMgCB) void k_mg_modes(CoarseArgs a) {
+  __shared__ double red[kMgCB], x[kMgSmall], lds[kMgCB / kWave];
+  const int s = blockIdx.z, k = blockIdx.x, n = a.nyc, m = a.nxc;
+  if (a.flags[s] != DONE_NO) return;
+  const int t = threadIdx.x, j = t & (kMgSmall - 1), q0 = (t / kMgSmall) * kMgPer;
+  const auto bs = make_rsrc(a.b + (size_t)s * a.Nc, (uint64_t)a.Nc * 4);
+  float bv[kMgPer];
+  double psi[kMgPer], psiT[kMgPer];
+#pragma unroll
+  for (int u = 0; u < kMgPer; ++u)
+    bv[u] = bload(bs, (j < n && q0 + u < m) ? (uint32_t)((q0 + u) * n + j) * 4u : kOOB);
+  const double ph = t < m ? a.phiT[(size_t)k * m + t] : 0.0;
+  double mean = 0.0;
+  for (int u = t; u < a.bP; u += kMgCB) mean += a.bpart[(size_t)s * a.bP + u];
+  const double dinv = j < n ? a.dinv[(size_t)j * m + k] : 0.0;
+  mg_load_col(a.psi, n, j, q0, psi);
+  mg_load_col(a.psiT, n, j, q0, psiT);
+  __builtin_amdgcn_sched_barrier(0);  // all loads in flight before the first sum
+  mean = wave_sum_dpp(mean);
+  if ((t & (kWave - 1)) == 0) lds[t / kWave] = mean;
+  if (t < kMgSmall) x[t] = ph;
+  __syncthreads();
+  mean = 0.0;
+#pragma unroll
+  for (int w = 0; w < kMgCB / kWave; ++w) mean += lds[w];
+  mean /= (double)a.Nc;
+  double bd[kMgPer];
+#pragma unroll
+  for (int u = 0; u < kMgPer; ++u) bd[u] = (double)bv[u] - mean;  // phi is 0 past m
+  const double T = mg_dot_parts(bd, x, q0, red);
+  if (t < kMgSmall) x[t] = t < n ? T : 0.0;
+  __syncthreads();
+  const double U = mg_dot_parts(psi, x, q0, red) * dinv;
+  if (t < kMgSmall) x[t] = U;  // dinv is 0 past n
+  __syncthreads();
+  const double V = mg_dot_parts(psiT, x, q0, red);
+  if (t < n) a.bh[(size_t)s * a.Nc + (size_t)t * m + k] = V;
+}
+
+// Row j of the solution, x[j][i] = sum_k phi[i][k] bh[j][k], and its sum (the
+// fine level's prolongation removes the mean); one workgroup per row.
+__global__ __launch_bounds__(kMgCB) void k_mg_back(CoarseArgs a) {
+  __shared__ double red[kMgCB], c[kMgSmall], lds[kWaves];
+  const int s = blockIdx.z, j = blockIdx.x, m = a.nxc;
+  if (a.flags[s] != DONE_NO) return;
+  const int t = threadIdx.x, i = t & (kMgSmall - 1), q0 = (t / kMgSmall) * kMgPer;
+  const double cv = t < m ? a.bh[(size_t)s * a.Nc + (size_t)j * m + t] : 0.0;
+  double phiT[kMgPer];
+  mg_load_col(a.phiT, m, i, q0, phiT);
+  __builtin_amdgcn_sched_barrier(0);
+  if (t < kMgSmall) c[t] = cv;
+  __syncthreads();
+  const float x = (float)mg_dot_parts(phiT, c, q0, red);
+  if (t < m) a.x[(size_t)s * a.Nc + (size_t)j * m + t] = x;
+  const double sum = wave_sum_dpp(t < m ? (double)x : 0.0);
+  if ((t & (kWave - 1)) == 0 && t < kMgSmall) lds[t / kWave] = sum;
+  __syncthreads();
+  if (t == 0) a.xpart[(size_t)s * a.nyc + j] = lds[0] + lds[1];
+}
+
 // ---------------------------------------------------------------------------
 #define PPE_MG_DISPATCH(R, ...)                                  \
   switch (R) {                                                   \
@@ -386,6 +487,8 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
   const MgData& m = *pa.mg;
   const int L = m.L;
   const Cheb k = cheb_consts();
+  // the two-launch coarsest solve reads a transposed right-hand side
+  const bool small = L > 1 && m.nxc <= kMgSmall && m.nyc <= kMgSmall;
   auto rows = [&](int l) { return mg_rows((int64_t)m.lv[l].nx * m.lv[l].ny * nb); };
   // level l's arguments; the fine level reads the PCG residual and writes z
   auto level = [&](int l) {
@@ -405,6 +508,7 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
       a.nxc = c.nx;
       a.Nc = (int64_t)c.nx * c.ny;
       a.coarsest = l + 1 == L - 1;
+      a.bc_t = a.coarsest && small;
       a.bpart = m.bpart;
       a.xpart = m.xpart;
       a.nyc = c.ny;
@@ -435,10 +539,15 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
     ca.bP = L == 1 ? 1 : mg_tiles(m.lv[L - 2].nx, m.lv[L - 2].ny, rows(L - 2));
     ca.xpart = m.xpart;
     ca.flags = pa.flags;
-    const size_t shm = sizeof(double) * m.nxc;
-    k_mg_cfwd<<<dim3(m.nyc, 1, nb), kBlock, shm, s>>>(ca);
-    k_mg_ccol<<<dim3(m.nxc, 1, nb), kBlock, sizeof(double) * 2 * m.nyc, s>>>(ca);
-    k_mg_cbwd<<<dim3(m.nyc, 1, nb), kBlock, shm, s>>>(ca);
+    if (small) {
+      k_mg_modes<<<dim3(m.nxc, 1, nb), kMgCB, 0, s>>>(ca);
+      k_mg_back<<<dim3(m.nyc, 1, nb), kMgCB, 0, s>>>(ca);
+    } else {
+      const size_t shm = sizeof(double) * m.nxc;
+      k_mg_cfwd<<<dim3(m.nyc, 1, nb), kBlock, shm, s>>>(ca);
+      k_mg_ccol<<<dim3(m.nxc, 1, nb), kBlock, sizeof(double) * 2 * m.nyc, s>>>(ca);
+      k_mg_cbwd<<<dim3(m.nyc, 1, nb), kBlock, shm, s>>>(ca);
+    }
   }
   if (L == 1) {
     LevelArgs a = level(0);
