@@ -36,35 +36,6 @@ namespace ppe {
 // written to the 2x nearest-upsampled pixels of a finer level.
 constexpr int kCTH = 16, kCTW = 16;  // pixel tile of the convolution kernel
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-// Two BF16 values (one word) times one factor each, back to BF16 by one
-// packed round-to-nearest-even conversion.
-__device__ __forceinline__ uint32_t mul_bf16x2(uint32_t v, float lo, float hi) {
-  const float a = __builtin_bit_cast(float, v << 16) * lo;
-  const float b = __builtin_bit_cast(float, v & 0xffff0000u) * hi;
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
-}
-
-// Eight BF16 values times eight BF16 weights (one local weight per input channel).
-__device__ __forceinline__ uint4 mul_bf16x8(uint4 v, uint4 e) {
-  auto lo = [](uint32_t w) { return __builtin_bit_cast(float, w << 16); };
-  auto hi = [](uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); };
-  return make_uint4(mul_bf16x2(v.x, lo(e.x), hi(e.x)), mul_bf16x2(v.y, lo(e.y), hi(e.y)),
-                    mul_bf16x2(v.z, lo(e.z), hi(e.z)), mul_bf16x2(v.w, lo(e.w), hi(e.w)));
-}
-
-// Eight BF16 values times one BF16 weight (one local weight per node).
-__device__ __forceinline__ uint4 mul_bf16x8_s(uint4 v, uint32_t e16) {
-  const float e = __builtin_bit_cast(float, e16 << 16);
-  return make_uint4(mul_bf16x2(v.x, e, e), mul_bf16x2(v.y, e, e), mul_bf16x2(v.z, e, e), mul_bf16x2(v.w, e, e));
-}
-
-// Local-weight forms of a convolution: none, one per input channel (a map
-// laid out as the input), one per node (a [H][W] map).
-enum { kEtaNone = 0, kEtaChannel = 1, kEtaNode = 2 };
-
 template <int TN, int TAPS>
 struct ConvShape {
   static constexpr int HALO = TAPS == 9 ? 1 : 0;

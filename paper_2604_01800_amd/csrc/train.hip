@@ -208,12 +208,12 @@ static ppe_status train_state(ppe_net* n, int nb, int nx, int ny) {
   return PPE_OK;
 }
 
-static int wgrad_splits(int cout, int cin8, int taps, int64_t tiles, int64_t cap) {
-  const int tb = taps == 1 ? 128 : 32;  // channel tile of the 1x1 / 3x3 weight-gradient kernels
-  const int64_t blocks = (int64_t)((cout + tb - 1) / tb) * ((cin8 + tb - 1) / tb);
+// Splits of a 1x1 layer's weight gradient (128 x 128 channel tiles).
+static int wgrad_splits(int cout, int cin8, int64_t tiles, int64_t cap) {
+  const int64_t blocks = (int64_t)((cout + 127) / 128) * ((cin8 + 127) / 128);
   int64_t ns = std::max<int64_t>(1, 1024 / blocks);
   ns = std::min<int64_t>(ns, tiles);
-  ns = std::min<int64_t>(ns, cap / ((int64_t)cout * cin8 * taps));
+  ns = std::min<int64_t>(ns, cap / ((int64_t)cout * cin8));
   return (int)std::max<int64_t>(ns, 1);
 }
 
@@ -484,9 +484,14 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       g.dp_bstride = hw(l) * dp_pitch;
       g.e_bstride = hw(l) * (per_node ? 1 : cin8);
       g.eta_node = per_node;
-      const int ns = wgrad_splits(cout, cin8, taps, tiles_of(l), cap);
-      launch_wgrad(taps, g, dp, x, eta, part, ns, s);
-      launch_reduce_rows(part, ns, (int64_t)cout * cin * taps, 1.f, dG + oW, s);
+      if (taps == 9) {  // the bias follows the weights in the parameter vector
+        const int rows = launch_wgrad9(g, dp, x, eta, part, cap, s);
+        launch_reduce_rows(part, rows, (int64_t)cout * cin * 9 + cout, 1.f, dG + oW, s);
+      } else {
+        const int ns = wgrad_splits(cout, cin8, tiles_of(l), cap);
+        launch_wgrad1(g, dp, x, part, ns, s);
+        launch_reduce_rows(part, ns, (int64_t)cout * cin, 1.f, dG + oW, s);
+      }
     };
     auto bias = [&](int l, const bf16_t* d, int pitch, int C, int64_t ob) {
       launch_bias_grad(d, hw(l) * nb, pitch, 0, C, part, 1024, s);
@@ -536,12 +541,10 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       bf16_t* dD = G + t->g_d[l];
       launch_act_bwd(dD, ch(l), Ab + t->o_d[l], ch(l), 0, ch(l), hw(l) * nb, 1, s);
       wgrad(9, l, dD, ch(l), ch(l), Ab + t->o_c[l], md.cin8, md.cin, etap(t->e_d[l]), md.oW);
-      bias(l, dD, ch(l), ch(l), md.ob);
       dgrad(9, l, dD, ch(l), t->pT_d[l], t->kT_d[l], md.cin8, G + t->g_c[l]);
       eta_bwd(md, Ab + t->o_c[l], t->e_d[l], G + t->g_c[l]);
       launch_act_bwd(G + t->g_c[l], ch(l), Ab + t->o_c[l], ch(l), 0, ch(l), hw(l) * nb, 1, s);
       wgrad(9, l, G + t->g_c[l], ch(l), ch(l), Ab + t->o_cat[l], mc.cin8, mc.cin, etap(t->e_c[l]), mc.oW);
-      bias(l, G + t->g_c[l], ch(l), ch(l), mc.ob);
       dgrad(9, l, G + t->g_c[l], ch(l), t->pT_c[l], t->kT_c[l], mc.cin8, G + t->g_cat[l]);
       eta_bwd(mc, Ab + t->o_cat[l], t->e_c[l], G + t->g_cat[l]);
       launch_copy_ch(G + t->g_cat[l], t->p_cat[l], ch(l), G + t->g_E[l], ch(l), ch(l), hw(l) * nb, 0, s);
@@ -563,12 +566,10 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       else
         launch_act_bwd(dE, ch(l), Ab + t->o_cat[l], t->p_cat[l], ch(l), ch(l), hw(l) * nb, 1, s);
       wgrad(9, l, dE, ch(l), ch(l), Ab + t->o_a[l], mb.cin8, mb.cin, etap(t->e_b[l]), mb.oW);
-      bias(l, dE, ch(l), ch(l), mb.ob);
       dgrad(9, l, dE, ch(l), t->pT_b[l], t->kT_b[l], mb.cin8, G + t->g_a[l]);
       eta_bwd(mb, Ab + t->o_a[l], t->e_b[l], G + t->g_a[l]);
       launch_act_bwd(G + t->g_a[l], ch(l), Ab + t->o_a[l], ch(l), 0, ch(l), hw(l) * nb, 1, s);
       wgrad(9, l, G + t->g_a[l], ch(l), ch(l), Ab + t->o_in[l], ma.cin8, ma.cin, etap(t->e_a[l]), ma.oW);
-      bias(l, G + t->g_a[l], ch(l), ch(l), ma.ob);
       if (cfg.use_eta || l > 0) {
         dgrad(9, l, G + t->g_a[l], ch(l), t->pT_a[l], t->kT_a[l], ma.cin8, G + t->g_in[l]);
         eta_bwd(ma, Ab + t->o_in[l], t->e_a[l], G + t->g_in[l]);

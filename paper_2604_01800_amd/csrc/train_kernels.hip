@@ -12,15 +12,191 @@
 namespace ppe {
 
 // ---------------------------------------------------------------------------
-// Weight gradient of a convolution layer:
+// Matrix operands whose K dimension runs over pixels, read from an LDS tile
+// that keeps each pixel's channels together: ds_read_b64_tr_b16 gives lane i
+// of a 16-lane group the four values that column i of a 4 x 16 block holds,
+// where lane j points at the block's row j / 4, columns 4 (j % 4) .. + 3. Two of
+// them make the eight consecutive pixels of one MFMA 16x16x32 operand; p0 and
+// p1 point at the rows of pixels 0..3 and 4..7 of the lane's group.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+__device__ __forceinline__ bf16x8_t tr_frag(const bf16_t* p0, const bf16_t* p1) {
+  const s16x4_t a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p0);
+  const s16x4_t b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p1);
+  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Weight and bias gradients of a 3x3 layer:
 //   dW[co][ci][tap] = sum over pixels p of dPre[p][co] * Xbar[p + off(tap)][ci]
-// with Xbar = eta * X (the layer's weighted input). MFMA 16x16x32 BF16 with
-// A = dPre^T (M = 32 output channels per workgroup, K = pixels) and
-// B = shifted Xbar (N = 32 input channels per workgroup). Wave w owns the
-// (co, ci) sub-tile (w / 2, w % 2) for all taps. Each workgroup (split z)
-// accumulates 8 x 16 pixel tiles z, z + nsplit, ... of all samples and writes
-// its partial sums in the master layout [co][ci < cin][tap]; k_reduce_rows
-// sums the splits in a fixed order.
+//   db[co] = sum over pixels of dPre[p][co]
+// with Xbar = eta * X (the layer's weighted input), on MFMA 16x16x32 BF16 with
+// A = dPre^T (M = 16 MT output channels, K = pixels) and B = shifted Xbar (N = 16
+// input channels). A workgroup owns 16 MT output and 16 CT input channels;
+// wave w takes input tile w % CT and the K-steps w / CT, w / CT + 4 / CT, ... of
+// each 8 x 16 pixel tile, so one set of B operands (nine shifted reads of the
+// staged tile, halo included) feeds MT MFMAs per tap. The bias is one more
+// column of B, all ones, for the workgroups of the first input channels.
+// Split z takes the pixel tiles z, z + nsplit, ... of all samples, the next
+// tile's loads in flight during the current one's MFMA loop, and leaves 4 / CT
+// partial rows in the parameters' layout [co][ci < cin][tap] | [co];
+// k_reduce_rows sums them in a fixed order. The workgroups of one split run on
+// one XCD (they read the same pixels).
+//
+// Bound by the matrix cores and LDS reads about equally (26 8-byte reads for 36
+// MFMAs per K-step with MT = 4). An earlier form kept transposed copies of
+// dPre and of three column shifts of Xbar in LDS for a 32 x 32 channel tile:
+// ten 16-byte reads for nine MFMAs, and transposes through registers. The 14
+// layers of 64 samples of 256 x 256: 7.9 -> 1.8 ms.
+template <int MT, int CT, int ETA>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(
+    WgradGeo g, const bf16_t* __restrict__ dp, const bf16_t* __restrict__ x, const bf16_t* __restrict__ eta,
+    float* __restrict__ part, int nbx, int nblk, int nsplit) {
+  constexpr int TH = 8, TW = 16, LW = TW + 2, NPX = (TH + 2) * LW;
+  constexpr int CO = 16 * MT, CI = 16 * CT, KW = 4 / CT;
+  // LDS pitches (bf16): four consecutive pixels' 32-byte pieces in distinct banks
+  constexpr int XP = CI == 16 ? 16 : CI + 16, DP = CO + 16;
+  constexpr int GX = CI / 8, GD = CO / 8;  // 8-channel groups of a staged pixel
+  constexpr int NX = (NPX * GX + 255) / 256, ND = (TH * TW * GD + 255) / 256;
+  __shared__ __attribute__((aligned(16))) bf16_t s_x[NPX * XP];
+  __shared__ __attribute__((aligned(16))) bf16_t s_d[TH * TW * DP];
+  // workgroup -> (split, channel block): consecutive workgroups go to
+  // consecutive XCDs, so the blocks of a split are eight apart (nsplit is a
+  // multiple of 8, or 1 to 7 with plain numbering)
+  const int b = blockIdx.x;
+  int split, blk;
+  if (nsplit % 8 == 0) {
+    split = (b & 7) + 8 * ((b >> 3) / nblk);
+    blk = (b >> 3) % nblk;
+  } else {
+    split = b / nblk;
+    blk = b - split * nblk;
+  }
+  const int co0 = (blk % nbx) * CO, ci0 = (blk / nbx) * CI;
+  const int tiles_x = (g.W + TW - 1) / TW, tiles_y = (g.H + TH - 1) / TH;
+  const int per = tiles_x * tiles_y, tiles = per * g.nb;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int ct = wv % CT, kw = wv / CT;
+
+  f32x4_t acc[9][MT], accb[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    accb[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+
+  uint4 vx[NX], vd[ND], ve[ETA == kEtaChannel ? NX : 1];
+  uint32_t ve1[ETA == kEtaNode ? NX : 1];
+  auto issue = [&](int t) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // the lane's offsets are recomputed per tile rather than kept in registers
+    const int smp = t / per, rem = t - smp * per;
+    const int py0 = (rem / tiles_x) * TH, px0 = (rem % tiles_x) * TW;
+    // resources based at the tile's first (halo) pixel: lanes outside the
+    // image or the channels get an offset past the end and read 0
+    const int64_t hp = (int64_t)(py0 - 1) * g.W + px0 - 1, pp = (int64_t)py0 * g.W + px0;
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(x + smp * g.x_bstride + hp * g.cin8), (short)0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(dp + smp * g.dp_bstride + pp * g.dp_pitch), (short)0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t er = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(ETA != kEtaNone ? eta + smp * g.e_bstride + hp * (ETA == kEtaChannel ? g.cin8 : 1) : x), (short)0, 0x7fffffff,
+        0x00020000);
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int u = tid + 256 * i, px = u / GX, c = ci0 + (u - px * GX) * 8;
+      const int ly = px / LW, lx = px - ly * LW, gy = py0 + ly - 1, gx = px0 + lx - 1;
+      const bool ok = px < NPX && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W && c < g.cin8;
+      const uint32_t rel = (uint32_t)(ly * g.W + lx);
+      const uint32_t o = ok ? (rel * (uint32_t)g.cin8 + (uint32_t)c) * 2u : 0x80000000u;
+      vx[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, (int)o, 0, 0));
+      if constexpr (ETA == kEtaChannel)
+        ve[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(er, (int)o, 0, 0));
+      if constexpr (ETA == kEtaNode)
+        ve1[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(er, (int)(ok ? rel * 2u : 0x80000000u), 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int u = tid + 256 * i, px = u / GD, c = co0 + (u - px * GD) * 8;
+      const int ly = px / TW, lx = px - ly * TW;
+      const bool ok = px < TH * TW && py0 + ly < g.H && px0 + lx < g.W && c < g.cout;
+      const uint32_t o = ok ? ((uint32_t)(ly * g.W + lx) * (uint32_t)g.dp_pitch + (uint32_t)c) * 2u : 0x80000000u;
+      vd[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(dr, (int)o, 0, 0));
+    }
+  };
+  auto commit = [&]() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int u = tid + 256 * i, px = u / GX, c8 = u - px * GX;
+      uint4 v = vx[i];
+      if constexpr (ETA == kEtaChannel) v = mul_bf16x8(v, ve[i]);
+      if constexpr (ETA == kEtaNode) v = mul_bf16x8_s(v, ve1[i]);
+      if (px < NPX) *(uint4*)(s_x + px * XP + c8 * 8) = v;
+    }
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int u = tid + 256 * i, px = u / GD, c8 = u - px * GD;
+      if (px < TH * TW) *(uint4*)(s_d + px * DP + c8 * 8) = vd[i];
+    }
+  };
+  // this lane's rows of the transposed reads: group q = lane / 16 holds the
+  // K-step's pixels 8 q .. 8 q + 7 (tile row q / 2, columns 8 (q % 2) ..)
+  const int q = lane >> 4, jr = (lane & 15) >> 2, jc = 4 * (lane & 3);
+  const bf16_t* ad = s_d + ((q >> 1) * TW + 8 * (q & 1) + jr) * DP + jc;
+  const bf16_t* ax = s_x + ((q >> 1) * LW + 8 * (q & 1) + jr) * XP + ct * 16 + jc;
+  bf16x8_t ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  const bool with_bias = ci0 == 0 && ct == 0;
+
+  if (split < tiles) issue(split);
+  for (int t = split; t < tiles; t += nsplit) {
+    __syncthreads();  // the previous tile's MFMA loop is done with LDS
+    commit();
+    __syncthreads();
+    if (t + nsplit < tiles) issue(t + nsplit);
+#pragma unroll
+    for (int si = 0; si < 4 / KW; ++si) {
+      const int st = kw + KW * si;  // tile rows 2 st, 2 st + 1
+      const bf16_t* pd = ad + st * 2 * TW * DP;
+      const bf16_t* px = ax + st * 2 * LW * XP;
+      bf16x8_t af[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) af[m] = tr_frag(pd + m * 16, pd + 4 * DP + m * 16);
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap) {
+        const int o = (tap / 3 * LW + tap % 3) * XP;
+        const bf16x8_t bf = tr_frag(px + o, px + o + 4 * XP);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[tap][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[m], bf, acc[tap][m], 0, 0, 0);
+      }
+      if (with_bias) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[m], ones, accb[m], 0, 0, 0);
+      }
+    }
+  }
+  // lane holds dW[co0 + 16 m + 4 (lane >> 4) + j][ci0 + 16 ct + (lane & 15)] per tap
+  const int ci = ci0 + ct * 16 + (lane & 15);
+  const int64_t len = (int64_t)g.cout * g.cin * 9 + g.cout;
+  float* ps = part + (int64_t)(split * KW + kw) * len;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int co = co0 + m * 16 + 4 * (lane >> 4) + j;
+      if (co >= g.cout) continue;
+      if (ci < g.cin) {
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) ps[((int64_t)co * g.cin + ci) * 9 + tap] = acc[tap][m][j];
+      }
+      if (with_bias && (lane & 15) == 0) ps[len - g.cout + co] = accb[m][j];
+    }
+}
+
 __device__ __forceinline__ void transpose8x8_bf16(const uint4 (&v)[8], uint4 (&w)[8]) {
   // v[r] holds channels 0..7 of pixel r; w[e] receives pixels 0..7 of channel e
 #pragma unroll
@@ -34,137 +210,6 @@ __device__ __forceinline__ void transpose8x8_bf16(const uint4 (&v)[8], uint4 (&w
       o[j] = (e & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
     }
     w[e] = make_uint4(o[0], o[1], o[2], o[3]);
-  }
-}
-
-template <int TAPS>
-__global__ __launch_bounds__(256) void k_wgrad(WgradGeo g, const bf16_t* __restrict__ dp, const bf16_t* __restrict__ x,
-                                               const bf16_t* __restrict__ eta, float* __restrict__ part) {
-  constexpr int HALO = TAPS == 9 ? 1 : 0;
-  constexpr int TH = 8, TW = 16, NP = TH * TW;
-  constexpr int LH = TH + 2 * HALO;
-  constexpr int NDX = TAPS == 9 ? 3 : 1;
-  constexpr int DPP = NP + 8;   // LDS pitch of a transposed dPre row
-  constexpr int XPP = TW + 8;   // LDS pitch of a staged input row
-  constexpr int CIP = LH * XPP + 8;  // LDS pitch of one input channel's rows (16 lanes in distinct banks)
-  // staging units of 8 pixels x 8 channels, each loaded with 16-byte loads,
-  // transposed in registers and written as 16-byte LDS rows: dPre (4 channel
-  // groups x 16 pixel octets), then the weighted input (NDX column shifts x 4
-  // channel groups x LH rows x 2 column octets)
-  constexpr int NUD = 4 * (NP / 8), NUXS = NDX * 4 * LH * (TW / 8);
-  constexpr int NUS = NUD + NUXS, RND = (NUS + 255) / 256;
-  __shared__ __attribute__((aligned(16))) bf16_t s_dp[32 * DPP];
-  __shared__ __attribute__((aligned(16))) bf16_t s_x[NDX * 32 * CIP];
-  const int co0 = blockIdx.x * 32, ci0 = blockIdx.y * 32;
-  const int split = blockIdx.z, nsplit = gridDim.z;
-  const int tiles_x = (g.W + TW - 1) / TW, tiles_y = (g.H + TH - 1) / TH;
-  const int tiles = tiles_x * tiles_y * g.nb;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int mt = wv >> 1, nt = wv & 1;
-  f32x4_t acc[TAPS];
-#pragma unroll
-  for (int t = 0; t < TAPS; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  for (int t = split; t < tiles; t += nsplit) {
-    const int smp = t / (tiles_x * tiles_y);
-    const int rem = t - smp * tiles_x * tiles_y;
-    const int py0 = (rem / tiles_x) * TH, px0 = (rem % tiles_x) * TW;
-    const bf16_t* dps = dp + (int64_t)smp * g.dp_bstride;
-    const bf16_t* xs = x + (int64_t)smp * g.x_bstride;
-    const bf16_t* es = eta ? eta + (int64_t)smp * g.e_bstride : nullptr;
-    __syncthreads();  // the previous tile's MFMA loop is done with LDS
-#pragma unroll
-    for (int rd = 0; rd < RND; ++rd) {
-      const int u = threadIdx.x + 256 * rd;
-      if (u >= NUS) continue;
-      uint4 v[8], w[8];
-      if (u < NUD) {
-        // dPre: channel group cg of pixels 8 oct .. 8 oct + 7 (one tile row)
-        const int cg = u & 3, oct = u >> 2;
-        const int py = py0 + (oct * 8) / TW, pxb = px0 + (oct * 8) % TW;
-        const bool ok = py < g.H && co0 + cg * 8 < g.cout;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          v[r] = make_uint4(0, 0, 0, 0);
-          if (ok && pxb + r < g.W)
-            v[r] = *(const uint4*)(dps + ((int64_t)py * g.W + pxb + r) * g.dp_pitch + co0 + cg * 8);
-        }
-        transpose8x8_bf16(v, w);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) *(uint4*)(s_dp + (cg * 8 + e) * DPP + oct * 8) = w[e];
-      } else {
-        // weighted input, column shift dx: s_x[dx][ci][row][col] = Xbar[row - H][col + dx - H]
-        const int q = u - NUD;
-        const int oct = q & 1;
-        int r2 = q >> 1;
-        const int row = r2 % LH;
-        r2 /= LH;
-        const int cg = r2 % 4, dx = r2 / 4;
-        const int gy = py0 + row - HALO, gxb = px0 + oct * 8 + dx - HALO;
-        const bool ok = gy >= 0 && gy < g.H && ci0 + cg * 8 < g.cin8;
-        uint4 ev[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          v[r] = make_uint4(0, 0, 0, 0);
-          ev[r] = make_uint4(0, 0, 0, 0);
-          const int gx = gxb + r;
-          if (ok && gx >= 0 && gx < g.W) {
-            const int64_t pix = (int64_t)gy * g.W + gx;
-            const int64_t off = pix * g.cin8 + ci0 + cg * 8;
-            v[r] = *(const uint4*)(xs + off);
-            if (es) {
-              if (g.eta_node) {  // one weight for the pixel's eight channels
-                const uint32_t e2 = (uint32_t)es[pix] * 0x10001u;
-                ev[r] = make_uint4(e2, e2, e2, e2);
-              } else {
-                ev[r] = *(const uint4*)(es + off);
-              }
-            }
-          }
-        }
-        if (es) {
-#pragma unroll
-          for (int r = 0; r < 8; ++r) {
-            const uint32_t a4[4] = {v[r].x, v[r].y, v[r].z, v[r].w}, b4[4] = {ev[r].x, ev[r].y, ev[r].z, ev[r].w};
-            uint32_t o4[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const float lo = bf2f((bf16_t)(a4[k] & 0xffff)) * bf2f((bf16_t)(b4[k] & 0xffff));
-              const float hi = bf2f((bf16_t)(a4[k] >> 16)) * bf2f((bf16_t)(b4[k] >> 16));
-              o4[k] = (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
-            }
-            v[r] = make_uint4(o4[0], o4[1], o4[2], o4[3]);
-          }
-        }
-        transpose8x8_bf16(v, w);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) *(uint4*)(s_x + (dx * 32 + cg * 8 + e) * CIP + row * XPP + oct * 8) = w[e];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int st = 0; st < NP / 32; ++st) {
-      const int pk = st * 32 + (lane >> 4) * 8;  // first of this lane's 8 pixels (same tile row)
-      const int prow = pk / TW, pcol = pk % TW;
-      const bf16x8_t afr = *(const bf16x8_t*)(s_dp + (mt * 16 + (lane & 15)) * DPP + pk);
-#pragma unroll
-      for (int tap = 0; tap < TAPS; ++tap) {
-        const int dy = TAPS == 9 ? tap / 3 : 0, dx = TAPS == 9 ? tap % 3 : 0;
-        const bf16x8_t bfr =
-            *(const bf16x8_t*)(s_x + (dx * 32 + nt * 16 + (lane & 15)) * CIP + (prow + dy) * XPP + pcol);
-        acc[tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr, bfr, acc[tap], 0, 0, 0);
-      }
-    }
-  }
-  // lane holds dW[co = co0 + mt*16 + 4*(lane>>4) + j][ci = ci0 + nt*16 + (lane&15)] per tap
-  const int ci = ci0 + nt * 16 + (lane & 15);
-  float* ps = part + (int64_t)split * g.cout * g.cin * TAPS;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int co = co0 + mt * 16 + 4 * (lane >> 4) + j;
-    if (co >= g.cout || ci >= g.cin) continue;
-#pragma unroll
-    for (int tap = 0; tap < TAPS; ++tap) ps[((int64_t)co * g.cin + ci) * TAPS + tap] = acc[tap][j];
   }
 }
 
@@ -904,16 +949,45 @@ __global__ __launch_bounds__(256) void k_sam_perturb(int64_t n, float* w, const 
 // ---------------------------------------------------------------------------
 static unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-void launch_wgrad(int taps, const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf16_t* eta, float* part,
-                  int nsplit, hipStream_t s) {
-  if (taps == 1 && !eta) {
-    const dim3 grid1((g.cout + kW1T - 1) / kW1T, (g.cin8 + kW1T - 1) / kW1T, nsplit);
-    k_wgrad1<<<grid1, 256, 0, s>>>(g, dp, x, part);
-    return;
+void launch_wgrad1(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, float* part, int nsplit, hipStream_t s) {
+  const dim3 grid1((g.cout + kW1T - 1) / kW1T, (g.cin8 + kW1T - 1) / kW1T, nsplit);
+  k_wgrad1<<<grid1, 256, 0, s>>>(g, dp, x, part);
+}
+
+// Channel tiles of k_wgrad9: 64 output channels per workgroup where the layer
+// has more than 32, and of 64, 32 or 16 input channels the widest that pads the
+// input least (a 16-channel tile leaves four K-splits per workgroup, so only
+// for inputs of at most 16). Splits: two workgroups per compute unit, at most one per
+// pixel tile, and as many rows as the partials buffer holds.
+int launch_wgrad9(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf16_t* eta, float* part, int64_t cap,
+                  hipStream_t s) {
+  const int mt = g.cout > 32 ? 4 : 2;
+  const int ct = g.cin8 <= 16 ? 1 : (g.cin8 + 63) / 64 * 64 > (g.cin8 + 31) / 32 * 32 ? 2 : 4;
+  const int kw = 4 / ct;
+  const int nbx = (g.cout + 16 * mt - 1) / (16 * mt), nblk = nbx * ((g.cin8 + 16 * ct - 1) / (16 * ct));
+  const int64_t tiles = (int64_t)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.nb;
+  const int64_t len = (int64_t)g.cout * g.cin * 9 + g.cout;
+  int64_t ns = std::min<int64_t>(std::min<int64_t>(tiles, std::max(1, 512 / nblk)), cap / (len * kw));
+  if (ns > 8) ns = ns / 8 * 8;
+  ns = std::max<int64_t>(ns, 1);
+  const unsigned grid = (unsigned)(ns * nblk);
+#define PPE_WG9(MT, CT, ETA) k_wgrad9<MT, CT, ETA><<<grid, 256, 0, s>>>(g, dp, x, eta, part, nbx, nblk, (int)ns)
+#define PPE_WG9_ETA(MT, CT)                            \
+  if (!eta) PPE_WG9(MT, CT, kEtaNone);                 \
+  else if (g.eta_node) PPE_WG9(MT, CT, kEtaNode);      \
+  else PPE_WG9(MT, CT, kEtaChannel)
+  if (mt == 4) {
+    if (ct == 4) { PPE_WG9_ETA(4, 4); }
+    else if (ct == 2) { PPE_WG9_ETA(4, 2); }
+    else { PPE_WG9_ETA(4, 1); }
+  } else {
+    if (ct == 4) { PPE_WG9_ETA(2, 4); }
+    else if (ct == 2) { PPE_WG9_ETA(2, 2); }
+    else { PPE_WG9_ETA(2, 1); }
   }
-  const dim3 grid((g.cout + 31) / 32, (g.cin8 + 31) / 32, nsplit);
-  if (taps == 9) k_wgrad<9><<<grid, 256, 0, s>>>(g, dp, x, eta, part);
-  else k_wgrad<1><<<grid, 256, 0, s>>>(g, dp, x, eta, part);
+#undef PPE_WG9_ETA
+#undef PPE_WG9
+  return (int)ns * kw;
 }
 
 void launch_reduce_rows(const float* part, int nparts, int64_t len, float scale, float* out, hipStream_t s) {

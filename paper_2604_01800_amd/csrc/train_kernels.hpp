@@ -14,8 +14,12 @@ struct WgradGeo {
   int eta_node;       // 1: eta holds one weight per pixel ([H][W] per sample), else one per input channel
 };
 
-void launch_wgrad(int taps, const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf16_t* eta, float* part,
-                  int nsplit, hipStream_t s);
+// Partial rows of a 1x1 layer's weight gradient ([cout][cin] each).
+void launch_wgrad1(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, float* part, int nsplit, hipStream_t s);
+// Partial rows of a 3x3 layer's weight and bias gradients
+// ([cout][cin][9] | [cout] each, at most cap floats in all); returns their number.
+int launch_wgrad9(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf16_t* eta, float* part, int64_t cap,
+                  hipStream_t s);
 void launch_reduce_rows(const float* part, int nparts, int64_t len, float scale, float* out, hipStream_t s);
 void launch_bias_grad(const bf16_t* d, int64_t npix, int pitch, int off, int C, float* part, int nparts,
                       hipStream_t s);
