@@ -32,16 +32,16 @@ __device__ __forceinline__ bf16x8_t tr_frag(const bf16_t* p0, const bf16_t* p1) 
 //   db[co] = sum over pixels of dPre[p][co]
 // with Xbar = eta * X (the layer's weighted input), on MFMA 16x16x32 BF16 with
 // A = dPre^T (M = 16 MT output channels, K = pixels) and B = shifted Xbar (N = 16
-// input channels). A workgroup owns 16 MT output and 16 CT input channels;
-// wave w takes input tile w % CT and the K-steps w / CT, w / CT + 4 / CT, ... of
-// each 8 x 16 pixel tile, so one set of B operands (nine shifted reads of the
-// staged tile, halo included) feeds MT MFMAs per tap. The bias is one more
-// column of B, all ones, for the workgroups of the first input channels.
-// Split z takes the pixel tiles z, z + nsplit, ... of all samples, the next
-// tile's loads in flight during the current one's MFMA loop, and leaves 4 / CT
-// partial rows in the parameters' layout [co][ci < cin][tap] | [co];
-// k_reduce_rows sums them in a fixed order. The workgroups of one split run on
-// one XCD (they read the same pixels).
+// input channels). A workgroup of CT wavefronts owns 16 MT output and 16 CT
+// input channels, wave w the input channels 16 w .. + 15; one set of B operands
+// (nine shifted reads of the staged 8 x 16 pixel tile, halo included) feeds MT
+// MFMAs per tap. The bias is one more column of B, all ones, for the workgroups
+// of the first input channels. Split z takes the pixel tiles z, z + nsplit, ...
+// of all samples, the next tile's loads in flight during the current one's MFMA
+// loop, and leaves a partial row in the parameters' layout
+// [co][ci < cin][tap] | [co]; k_reduce_rows sums the rows in a fixed order. The
+// workgroups of one split run on one XCD (they read the same pixels). The
+// order of every sum depends on nsplit alone, not on the channel tiles.
 //
 // Bound by the matrix cores and LDS reads about equally (26 8-byte reads for 36
 // MFMAs per K-step with MT = 4). An earlier form kept transposed copies of
@@ -49,34 +49,32 @@ __device__ __forceinline__ bf16x8_t tr_frag(const bf16_t* p0, const bf16_t* p1) 
 // ten 16-byte reads for nine MFMAs, and transposes through registers. The 14
 // layers of 64 samples of 256 x 256: 7.9 -> 1.8 ms.
 template <int MT, int CT, int ETA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(
+__global__ __launch_bounds__(64 * CT) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad9(
     WgradGeo g, const bf16_t* __restrict__ dp, const bf16_t* __restrict__ x, const bf16_t* __restrict__ eta,
     float* __restrict__ part, int nbx, int nblk, int nsplit) {
   constexpr int TH = 8, TW = 16, LW = TW + 2, NPX = (TH + 2) * LW;
-  constexpr int CO = 16 * MT, CI = 16 * CT, KW = 4 / CT;
+  constexpr int CO = 16 * MT, CI = 16 * CT, NT = 64 * CT;
   // LDS pitches (bf16): four consecutive pixels' 32-byte pieces in distinct banks
   constexpr int XP = CI == 16 ? 16 : CI + 16, DP = CO + 16;
   constexpr int GX = CI / 8, GD = CO / 8;  // 8-channel groups of a staged pixel
-  constexpr int NX = (NPX * GX + 255) / 256, ND = (TH * TW * GD + 255) / 256;
+  constexpr int NX = (NPX * GX + NT - 1) / NT, ND = (TH * TW * GD + NT - 1) / NT;
   __shared__ __attribute__((aligned(16))) bf16_t s_x[NPX * XP];
   __shared__ __attribute__((aligned(16))) bf16_t s_d[TH * TW * DP];
-  // workgroup -> (split, channel block): consecutive workgroups go to
-  // consecutive XCDs, so the blocks of a split are eight apart (nsplit is a
-  // multiple of 8, or 1 to 7 with plain numbering)
-  const int b = blockIdx.x;
+  // workgroup -> (split, channel block): workgroup b runs on XCD b % 8, so
+  // within groups of eight splits the blocks of a split are eight apart
+  const int b = blockIdx.x, full = nsplit / 8 * 8 * nblk;
   int split, blk;
-  if (nsplit % 8 == 0) {
+  if (b < full) {
     split = (b & 7) + 8 * ((b >> 3) / nblk);
     blk = (b >> 3) % nblk;
   } else {
-    split = b / nblk;
-    blk = b - split * nblk;
+    split = nsplit / 8 * 8 + (b - full) / nblk;
+    blk = (b - full) % nblk;
   }
   const int co0 = (blk % nbx) * CO, ci0 = (blk / nbx) * CI;
   const int tiles_x = (g.W + TW - 1) / TW, tiles_y = (g.H + TH - 1) / TH;
   const int per = tiles_x * tiles_y, tiles = per * g.nb;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int ct = wv % CT, kw = wv / CT;
+  const int lane = threadIdx.x & 63, ct = threadIdx.x >> 6;
 
   f32x4_t acc[9][MT], accb[MT];
 #pragma unroll
@@ -105,7 +103,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         0x00020000);
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-      const int u = tid + 256 * i, px = u / GX, c = ci0 + (u - px * GX) * 8;
+      const int u = tid + NT * i, px = u / GX, c = ci0 + (u - px * GX) * 8;
       const int ly = px / LW, lx = px - ly * LW, gy = py0 + ly - 1, gx = px0 + lx - 1;
       const bool ok = px < NPX && gy >= 0 && gy < g.H && gx >= 0 && gx < g.W && c < g.cin8;
       const uint32_t rel = (uint32_t)(ly * g.W + lx);
@@ -118,7 +116,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
-      const int u = tid + 256 * i, px = u / GD, c = co0 + (u - px * GD) * 8;
+      const int u = tid + NT * i, px = u / GD, c = co0 + (u - px * GD) * 8;
       const int ly = px / TW, lx = px - ly * TW;
       const bool ok = px < TH * TW && py0 + ly < g.H && px0 + lx < g.W && c < g.cout;
       const uint32_t o = ok ? ((uint32_t)(ly * g.W + lx) * (uint32_t)g.dp_pitch + (uint32_t)c) * 2u : 0x80000000u;
@@ -130,7 +128,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     asm volatile("" : "+v"(tid));
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-      const int u = tid + 256 * i, px = u / GX, c8 = u - px * GX;
+      const int u = tid + NT * i, px = u / GX, c8 = u - px * GX;
       uint4 v = vx[i];
       if constexpr (ETA == kEtaChannel) v = mul_bf16x8(v, ve[i]);
       if constexpr (ETA == kEtaNode) v = mul_bf16x8_s(v, ve1[i]);
@@ -138,7 +136,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
-      const int u = tid + 256 * i, px = u / GD, c8 = u - px * GD;
+      const int u = tid + NT * i, px = u / GD, c8 = u - px * GD;
       if (px < TH * TW) *(uint4*)(s_d + px * DP + c8 * 8) = vd[i];
     }
   };
@@ -159,8 +157,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     __syncthreads();
     if (t + nsplit < tiles) issue(t + nsplit);
 #pragma unroll
-    for (int si = 0; si < 4 / KW; ++si) {
-      const int st = kw + KW * si;  // tile rows 2 st, 2 st + 1
+    for (int st = 0; st < 4; ++st) {  // tile rows 2 st, 2 st + 1
       const bf16_t* pd = ad + st * 2 * TW * DP;
       const bf16_t* px = ax + st * 2 * LW * XP;
       bf16x8_t af[MT];
@@ -182,7 +179,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   // lane holds dW[co0 + 16 m + 4 (lane >> 4) + j][ci0 + 16 ct + (lane & 15)] per tap
   const int ci = ci0 + ct * 16 + (lane & 15);
   const int64_t len = (int64_t)g.cout * g.cin * 9 + g.cout;
-  float* ps = part + (int64_t)(split * KW + kw) * len;
+  float* ps = part + (int64_t)split * len;
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -954,24 +951,24 @@ void launch_wgrad1(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, float* 
   k_wgrad1<<<grid1, 256, 0, s>>>(g, dp, x, part);
 }
 
-// Channel tiles of k_wgrad9: 64 output channels per workgroup where the layer
-// has more than 32, and of 64, 32 or 16 input channels the widest that pads the
-// input least (a 16-channel tile leaves four K-splits per workgroup, so only
-// for inputs of at most 16). Splits: two workgroups per compute unit, at most one per
-// pixel tile, and as many rows as the partials buffer holds.
+// Splits and channel tiles of k_wgrad9. Splits: 1024 / (32 x 32 channel tiles of
+// the layer), at most one per pixel tile, and as many rows as the partials
+// buffer holds. Per workgroup 64, 32 or 16 input channels, the widest that pads
+// the input least; 64 output channels where that leaves two
+// workgroups per compute unit, else 32 (64 samples of 256 x 256: 25.1 ms a step, 25.4 with 64 from one per unit).
 int launch_wgrad9(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf16_t* eta, float* part, int64_t cap,
                   hipStream_t s) {
-  const int mt = g.cout > 32 ? 4 : 2;
-  const int ct = g.cin8 <= 16 ? 1 : (g.cin8 + 63) / 64 * 64 > (g.cin8 + 31) / 32 * 32 ? 2 : 4;
-  const int kw = 4 / ct;
-  const int nbx = (g.cout + 16 * mt - 1) / (16 * mt), nblk = nbx * ((g.cin8 + 16 * ct - 1) / (16 * ct));
   const int64_t tiles = (int64_t)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.nb;
   const int64_t len = (int64_t)g.cout * g.cin * 9 + g.cout;
-  int64_t ns = std::min<int64_t>(std::min<int64_t>(tiles, std::max(1, 512 / nblk)), cap / (len * kw));
-  if (ns > 8) ns = ns / 8 * 8;
-  ns = std::max<int64_t>(ns, 1);
+  const int64_t blocks32 = (int64_t)((g.cout + 31) / 32) * ((g.cin8 + 31) / 32);
+  const int64_t ns =
+      std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(1, 1024 / blocks32), tiles, cap / len}));
+  const int ct = g.cin8 <= 16 ? 1 : (g.cin8 + 63) / 64 * 64 > (g.cin8 + 31) / 32 * 32 ? 2 : 4;
+  const int nby = (g.cin8 + 16 * ct - 1) / (16 * ct);
+  const int mt = g.cout > 32 && ns * ((g.cout + 63) / 64) * nby >= 512 ? 4 : 2;
+  const int nbx = (g.cout + 16 * mt - 1) / (16 * mt), nblk = nbx * nby;
   const unsigned grid = (unsigned)(ns * nblk);
-#define PPE_WG9(MT, CT, ETA) k_wgrad9<MT, CT, ETA><<<grid, 256, 0, s>>>(g, dp, x, eta, part, nbx, nblk, (int)ns)
+#define PPE_WG9(MT, CT, ETA) k_wgrad9<MT, CT, ETA><<<grid, 64 * CT, 0, s>>>(g, dp, x, eta, part, nbx, nblk, (int)ns)
 #define PPE_WG9_ETA(MT, CT)                            \
   if (!eta) PPE_WG9(MT, CT, kEtaNone);                 \
   else if (g.eta_node) PPE_WG9(MT, CT, kEtaNode);      \
@@ -987,7 +984,7 @@ int launch_wgrad9(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf
   }
 #undef PPE_WG9_ETA
 #undef PPE_WG9
-  return (int)ns * kw;
+  return (int)ns;
 }
 
 void launch_reduce_rows(const float* part, int nparts, int64_t len, float scale, float* out, hipStream_t s) {
