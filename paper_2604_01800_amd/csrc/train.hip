@@ -40,7 +40,7 @@ struct TrainState {
   int64_t o_in[kMaxLevels] = {}, o_a[kMaxLevels] = {}, o_cat[kMaxLevels] = {}, o_c[kMaxLevels] = {},
           o_d[kMaxLevels] = {}, o_bot = 0, o_B = 0, o_T = 0, o_t0 = 0, o_h[9] = {};
   int64_t g_in[kMaxLevels] = {}, g_a[kMaxLevels] = {}, g_cat[kMaxLevels] = {}, g_c[kMaxLevels] = {},
-          g_d[kMaxLevels] = {}, g_E[kMaxLevels] = {}, g_Uc[kMaxLevels] = {}, g_bot = 0, g_B = 0, g_T = 0,
+          g_d[kMaxLevels] = {}, g_E[kMaxLevels] = {}, g_Uc[kMaxLevels] = {}, g_bot = 0, g_B = 0,
           g_h[9] = {};
   int64_t e_a[kMaxLevels] = {}, e_b[kMaxLevels] = {}, e_c[kMaxLevels] = {}, e_d[kMaxLevels] = {};
   // packed BF16 weights for this step: transposed (input gradients) per layer,
@@ -51,7 +51,7 @@ struct TrainState {
   int kT_a[kMaxLevels] = {}, kT_b[kMaxLevels] = {}, kT_c[kMaxLevels] = {}, kT_d[kMaxLevels] = {},
       kT_up[kMaxLevels] = {}, kT_head = 0, kT_tr[9] = {}, kF_head = 0, kF_tr[9] = {};
   // FP32 / FP64 vectors and partial sums
-  float* f32 = nullptr;  // y, Ay, res, gAy: [4][nb][N]
+  float* f32 = nullptr;  // y, Ay, res, gAy, y / gamma: [5][nb][N]
   float* part = nullptr;
   int64_t part_len = 0;
   double* dpart = nullptr;  // [nb][kRedBlocks] input-scale partials, then loss partials and the loss value
@@ -148,8 +148,7 @@ static ppe_status train_state(ppe_net* n, int nb, int nx, int ny) {
   t->o_T = A(ao, 0, P);
   t->o_t0 = A(ao, 0, 8);
   for (int k = 0; k < cfg.trunk_hidden; ++k) t->o_h[k] = A(ao, 0, TWd);
-  t->g_B = A(go, 0, P);
-  t->g_T = A(go, 0, P);
+  if (!bwd1x1_fits(P, cfg.base_channels)) t->g_B = A(go, 0, P);
   for (int k = 0; k < cfg.trunk_hidden; ++k) t->g_h[k] = A(go, 0, TWd);
   // packed weights of this step
   int64_t po = 0;
@@ -190,12 +189,12 @@ static ppe_status train_state(ppe_net* n, int nb, int nx, int ny) {
     t->pT_tr[k] = pk(cin8, t->kT_tr[k]);
   }
   const int64_t N = (int64_t)nx * ny;
-  t->part_len = (int64_t)16 << 20;  // floats
+  t->part_len = (int64_t)17 << 20;  // floats: 1024 rows of a 128 x 128 layer
   t->act = (bf16_t*)dev_alloc(ao * sizeof(bf16_t));
   t->grad = (bf16_t*)dev_alloc(go * sizeof(bf16_t));
   t->eta = cfg.use_eta ? (bf16_t*)dev_alloc(eo * sizeof(bf16_t)) : nullptr;
   t->packs = (bf16_t*)dev_alloc(po * sizeof(bf16_t));
-  t->f32 = (float*)dev_alloc(4 * N * nb * sizeof(float));
+  t->f32 = (float*)dev_alloc(5 * N * nb * sizeof(float));
   t->part = (float*)dev_alloc(t->part_len * sizeof(float));
   t->dpart = (double*)dev_alloc(((size_t)kRedBlocks * (nb + 1) + 8) * sizeof(double));
   t->d_coefs = (Coef*)dev_alloc(nb * sizeof(Coef));
@@ -403,6 +402,7 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
     float* Ay = y + N * nb;
     float* res = Ay + N * nb;
     float* gAy = res + N * nb;
+    float* ysum = gAy + N * nb;
     launch_input_pack(R, N, nb, t->dpart, Ab + t->o_in[0], t->p_in[0], N * t->p_in[0], s);
     for (int l = 0; l < L; ++l) {
       if (l > 0)
@@ -442,7 +442,7 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       launch_conv(1, false, geo(0, cin8, cout, cout, 0, k == TH ? 0 : 2), nb, src, nullptr, PK + t->pF_tr[k],
                   t->kF_tr[k], W + n->o_tb[k], dst, s);
     }
-    launch_don_fwd(N * nb, P, Ab + t->o_B, Ab + t->o_T, W + n->o_gamma, y, s);
+    launch_don_fwd(N * nb, P, Ab + t->o_B, Ab + t->o_T, W + n->o_gamma, y, ysum, s);
 
     float dscale = 1.f;
     if (supervised) {
@@ -494,7 +494,7 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       }
     };
     auto bias = [&](int l, const bf16_t* d, int pitch, int C, int64_t ob) {
-      launch_bias_grad(d, hw(l) * nb, pitch, 0, C, part, 1024, s);
+      launch_bias_grad(d, hw(l) * nb, pitch, 0, C, nullptr, nullptr, 0.f, part, 1024, s);
       launch_reduce_rows(part, 1024, C, 1.f, dG + ob, s);
     };
     auto dgrad = [&](int taps, int l, const bf16_t* dp, int cout_fwd, int64_t pT, int kT, int rows, bf16_t* out) {
@@ -517,21 +517,70 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       }
       launch_reduce_rows(part, np, len, 1.f, dG + m.oW1, s);
     };
-    // DeepONet contraction, head and trunk
-    launch_don_bwd(N * nb, P, Ab + t->o_B, Ab + t->o_T, W + n->o_gamma, gAy, dscale, G + t->g_B, G + t->g_T, part,
-                   2048, s);
-    launch_reduce_rows(part, 2048, 1, 1.f, dG + n->o_gamma, s);
-    wgrad(1, 0, G + t->g_B, P, P, Ab + t->o_d[0], C0, C0, nullptr, n->o_headW);
-    bias(0, G + t->g_B, P, P, n->o_headb);
-    dgrad(1, 0, G + t->g_B, P, t->pT_head, t->kT_head, C0, G + t->g_d[0]);
+    // whole backward of a 1x1 layer where it fits one pass, else its parts
+    auto bwd1 = [&](int l, Bwd1x1 b, int64_t oW) {
+      b.hw = (int)hw(l);
+      b.nb = nb;
+      if (bwd1x1_fits(b.cout, b.cin8)) {
+        const int64_t room = cap - 1024;  // the last 1024 floats: gamma's shares
+        b.gpart = part + room;
+        const int rows = launch_bwd1x1(b, tiles_of(l), part, room, s);
+        launch_reduce_rows(part, rows, (int64_t)b.cout * b.cin + b.cout, 1.f, dG + oW, s);
+        if (b.s) launch_reduce_rows(b.gpart, rows, 1, 1.f, dG + n->o_gamma, s);
+        return;
+      }
+      bf16_t* dd = const_cast<bf16_t*>(b.d);
+      if (b.gamma) {
+        dd = G + t->g_B;
+        launch_don_grad(hw(l) * nb, b.cout, b.d, b.gamma, b.dy, b.scale, b.s, dd, part, 2048, s);
+        launch_reduce_rows(part, 2048, 1, 1.f, dG + n->o_gamma, s);
+      }
+      wgrad(1, l, dd, b.cout, b.cout, b.x, b.cin8, b.cin, nullptr, oW);
+      bias(l, dd, b.cout, b.cout, oW + (int64_t)b.cout * b.cin);
+      if (!b.dx) return;
+      ConvGeo g = geo(l, b.cout, b.cin8, b.cin8, 0, 0);
+      launch_conv(1, false, g, nb, dd, nullptr, b.wT, b.Kp, nullptr, b.dx, s);
+      if (b.act) launch_act_bwd(b.dx, b.cin8, b.x, b.cin8, 0, b.cin8, hw(l) * nb, b.act, s);
+    };
+    // DeepONet contraction, head and trunk: the gradients of B and T are formed
+    // where they are read
+    {
+      Bwd1x1 b{};
+      b.cout = P;
+      b.cin = b.cin8 = C0;
+      b.d = Ab + t->o_T;
+      b.x = Ab + t->o_d[0];
+      b.wT = PK + t->pT_head;
+      b.Kp = t->kT_head;
+      b.act = 1;
+      b.dx = G + t->g_d[0];
+      b.gamma = W + n->o_gamma;
+      b.dy = gAy;
+      b.scale = dscale;
+      b.s = ysum;
+      bwd1(0, b, n->o_headW);
+      // the head's bias gradient, sum gamma dy T, nearly cancels (sum dy = 0): a
+      // pass of its own with short FP32 chains replaces the one above
+      launch_bias_grad(b.d, N * nb, P, 0, P, b.gamma, b.dy, b.scale, part, 1024, s);
+      launch_reduce_rows(part, 1024, P, 1.f, dG + n->o_headb, s);
+    }
     for (int k = TH; k >= 0; --k) {
-      const int cin8 = k == 0 ? 8 : TWd, cin = k == 0 ? 2 : TWd, cout = k == TH ? P : TWd;
-      bf16_t* dk = k == TH ? G + t->g_T : G + t->g_h[k];
-      if (k < TH) launch_act_bwd(dk, cout, Ab + t->o_h[k], cout, 0, cout, N * nb, 2, s);
-      const bf16_t* xin = k == 0 ? Ab + t->o_t0 : Ab + t->o_h[k - 1];
-      wgrad(1, 0, dk, cout, cout, xin, cin8, cin, nullptr, n->o_tW[k]);
-      bias(0, dk, cout, cout, n->o_tb[k]);
-      if (k > 0) dgrad(1, 0, dk, cout, t->pT_tr[k], t->kT_tr[k], cin8, G + t->g_h[k - 1]);
+      Bwd1x1 b{};
+      b.cout = k == TH ? P : TWd;
+      b.cin = k == 0 ? 2 : TWd;
+      b.cin8 = k == 0 ? 8 : TWd;
+      b.d = k == TH ? Ab + t->o_B : G + t->g_h[k];
+      if (k == TH) {
+        b.gamma = W + n->o_gamma;
+        b.dy = gAy;
+        b.scale = dscale;
+      }
+      b.x = k == 0 ? Ab + t->o_t0 : Ab + t->o_h[k - 1];
+      b.wT = PK + t->pT_tr[k];
+      b.Kp = t->kT_tr[k];
+      b.act = 2;
+      b.dx = k > 0 ? G + t->g_h[k - 1] : nullptr;
+      bwd1(0, b, n->o_tW[k]);
     }
     // decoder, finest level first
     for (int l = 0; l <= L - 2; ++l) {
@@ -539,7 +588,6 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       const MConvL& mc = n->dec_c[l];
       const UpL& u = n->up[l];
       bf16_t* dD = G + t->g_d[l];
-      launch_act_bwd(dD, ch(l), Ab + t->o_d[l], ch(l), 0, ch(l), hw(l) * nb, 1, s);
       wgrad(9, l, dD, ch(l), ch(l), Ab + t->o_c[l], md.cin8, md.cin, etap(t->e_d[l]), md.oW);
       dgrad(9, l, dD, ch(l), t->pT_d[l], t->kT_d[l], md.cin8, G + t->g_c[l]);
       eta_bwd(md, Ab + t->o_c[l], t->e_d[l], G + t->g_c[l]);
@@ -551,19 +599,23 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       launch_up_bwd(t->H[l + 1], t->W[l + 1], ch(l), G + t->g_cat[l], t->p_cat[l], hw(l) * t->p_cat[l],
                     G + t->g_Uc[l], hw(l + 1) * ch(l), nb, s);
       const bf16_t* src = (l == L - 2) ? Ab + t->o_bot : Ab + t->o_d[l + 1];
-      wgrad(1, l + 1, G + t->g_Uc[l], ch(l), ch(l), src, u.cin, u.cin, nullptr, u.oW);
-      bias(l + 1, G + t->g_Uc[l], ch(l), ch(l), u.ob);
-      bf16_t* dnext = (l == L - 2) ? G + t->g_bot : G + t->g_d[l + 1];
-      dgrad(1, l + 1, G + t->g_Uc[l], ch(l), t->pT_up[l], t->kT_up[l], u.cin, dnext);
+      Bwd1x1 b{};
+      b.cout = ch(l);
+      b.cin = b.cin8 = u.cin;
+      b.d = G + t->g_Uc[l];
+      b.x = src;
+      b.wT = PK + t->pT_up[l];
+      b.Kp = t->kT_up[l];
+      b.act = 1;
+      b.dx = (l == L - 2) ? G + t->g_bot : G + t->g_d[l + 1];
+      bwd1(l + 1, b, u.oW);
     }
     // encoder, coarsest level first
     for (int l = L - 1; l >= 0; --l) {
       const MConvL& mb = n->enc_b[l];
       const MConvL& ma = n->enc_a[l];
       bf16_t* dE = (l == L - 1) ? G + t->g_bot : G + t->g_E[l];
-      if (l == L - 1)
-        launch_act_bwd(dE, ch(l), Ab + t->o_bot, ch(l), 0, ch(l), hw(l) * nb, 1, s);
-      else
+      if (l < L - 1)
         launch_act_bwd(dE, ch(l), Ab + t->o_cat[l], t->p_cat[l], ch(l), ch(l), hw(l) * nb, 1, s);
       wgrad(9, l, dE, ch(l), ch(l), Ab + t->o_a[l], mb.cin8, mb.cin, etap(t->e_b[l]), mb.oW);
       dgrad(9, l, dE, ch(l), t->pT_b[l], t->kT_b[l], mb.cin8, G + t->g_a[l]);

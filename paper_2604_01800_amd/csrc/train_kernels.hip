@@ -304,6 +304,223 @@ __global__ __launch_bounds__(256) void k_wgrad1(WgradGeo g, const bf16_t* __rest
   }
 }
 
+// Whole backward of a 1x1 layer of at most 128 output and input channels (the
+// trunk, the head, the narrow up-convolutions) in one pass over its pixels:
+//   dW[co][ci] = sum_p d[p][co] x[p][ci],  db[co] = sum_p d[p][co],
+//   dx[p][ci]  = act'(x[p][ci]) * bf16(sum_co W[co][ci] d[p][co]),
+// where x is the layer's input and act' the derivative of the activation that
+// made it (1 for ReLU where x > 0, 1 - x^2 for tanh). d is read, or formed
+// from the DeepONet contraction y = gamma sum_k B_k T_k: d = bf16(gamma dy S)
+// with S the other factor (T for the head, B for the trunk output).
+// Stages of 64 pixels: d and x go to LDS as they lie in memory (channels of a
+// pixel together). dW and db take both operands by transposed reads (K = pixels;
+// wave w the quarter (w / 2, w % 2) of the channel square), dx takes d's rows
+// as they are and the weights from LDS (wave w the pixels 16 w ..); its result
+// replaces d in LDS and leaves as whole 16-byte pieces. The next stage's loads are in flight
+// meanwhile.
+// Bound by HBM: 768 B per pixel at 128 channels (d and x read, dx written) where
+// separate launches for dW, db, dx and act' moved 2 KB. At 4.2 M pixels a
+// 128 x 128 layer takes 870 us against 286 + 205 + 385 + 420.
+constexpr int kB1P = 64;     // pixels per stage
+constexpr int kB1C = 128;    // channels at most
+constexpr int kB1DP = kB1C + 16;  // LDS pitch (bf16) of a pixel: see k_wgrad9
+constexpr int kB1WP = kB1C + 8;   // LDS pitch of a weight row
+enum { kActNone = 0, kActRelu = 1, kActTanh = 2 };
+
+__device__ __forceinline__ uint4 scale8(uint4 a, float c) {
+  const uint32_t x[4] = {a.x, a.y, a.z, a.w};
+  uint32_t o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    o[e] = (uint32_t)f2bf(c * bf2f((bf16_t)(x[e] & 0xffff))) | ((uint32_t)f2bf(c * bf2f((bf16_t)(x[e] >> 16))) << 16);
+  return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_bwd1x1(Bwd1x1 g,
+                                                                                        float* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) bf16_t s_d[kB1P * kB1DP];
+  __shared__ __attribute__((aligned(16))) bf16_t s_x[kB1P * kB1DP];
+  __shared__ __attribute__((aligned(16))) bf16_t s_w[kB1C * kB1WP];
+  __shared__ double lds[kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int wm = wv >> 1, wn = wv & 1;
+  const int cout = g.cout, cin8 = g.cin8;
+  const int nks = (cout + 31) / 32;
+  const int sps = (g.hw + kB1P - 1) / kB1P;  // stages per sample
+  const int stages = sps * g.nb;
+  // channels past cout or cin8 that the products read are zero for the whole launch
+  for (int u = tid; u < kB1P * kB1DP / 8; u += 256) {
+    *(uint4*)(s_d + u * 8) = make_uint4(0, 0, 0, 0);
+    *(uint4*)(s_x + u * 8) = make_uint4(0, 0, 0, 0);
+  }
+  if (g.dx) {
+    const int kq = g.Kp / 8;
+    for (int u = tid; u < kB1C * kq; u += 256) {
+      const int r = u / kq, q = u - r * kq;
+      *(uint4*)(s_w + r * kB1WP + q * 8) =
+          r < cin8 ? *(const uint4*)(g.wT + (int64_t)r * g.Kp + q * 8) : make_uint4(0, 0, 0, 0);
+    }
+  }
+  f32x4_t acc[4][4], accb[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    accb[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  bf16x8_t ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  // staging: thread t holds the 8-channel group t % 16 of pixels t / 16 + 16 i
+  const int c8 = (tid & 15) * 8, pl = tid >> 4;
+  const bool dch = c8 < cout, xch = c8 < cin8;
+  const float gam = g.gamma ? g.gamma[0] : 0.f;
+  uint4 vd[4], vx[4];
+  float vg[4], vs = 0.f, vsg = 0.f;
+  int left = 0;  // pixels of the stage in flight
+  int64_t pst = 0;  // its first pixel
+  auto issue = [&](int st) {
+    const int smp = st / sps, k0 = (st - smp * sps) * kB1P;
+    const int64_t p0 = (int64_t)smp * g.hw + k0;
+    pst = p0;
+    left = min(kB1P, g.hw - k0);
+    const bf16_t* db = g.d + p0 * cout + c8;
+    const bf16_t* xb = g.x + p0 * cin8 + c8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = pl + 16 * i;
+      const bool ok = q < left;
+      vd[i] = make_uint4(0, 0, 0, 0);
+      vx[i] = make_uint4(0, 0, 0, 0);
+      vg[i] = 0.f;
+      if (ok && dch) vd[i] = *(const uint4*)(db + q * cout);
+      if (ok && xch) vx[i] = *(const uint4*)(xb + q * cin8);
+      if (ok && g.gamma) vg[i] = g.dy[p0 + q];
+    }
+    if (g.s && tid < left) {
+      vs = g.s[p0 + tid];
+      vsg = g.dy[p0 + tid];
+    } else {
+      vs = 0.f;
+    }
+  };
+  double dgam = 0.0;
+  // transposed reads of a K-step of 32 pixels: group lane / 16 holds pixels
+  // 8 (lane / 16) .. + 7
+  const int jr = (lane & 15) >> 2, jc = 4 * (lane & 3);
+  const bf16_t* td = s_d + (8 * (lane >> 4) + jr) * kB1DP + jc + wm * 64;
+  const bf16_t* tx = s_x + (8 * (lane >> 4) + jr) * kB1DP + jc + wn * 64;
+  const bf16_t* wrow = s_w + (lane & 15) * kB1WP + (lane >> 4) * 8;
+  bf16_t* drow = s_d + (16 * wv + (lane & 15)) * kB1DP;
+  const bf16_t* xrow = s_x + (16 * wv + (lane & 15)) * kB1DP;
+
+  if ((int)blockIdx.x < stages) issue(blockIdx.x);
+  for (int st = blockIdx.x; st < stages; st += gridDim.x) {
+    const int np = left;
+    const int64_t p0 = pst;
+    __syncthreads();  // the stage before has left LDS
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = pl + 16 * i;
+      if (dch) *(uint4*)(s_d + q * kB1DP + c8) = g.gamma ? scale8(vd[i], gam * (g.scale * vg[i])) : vd[i];
+      if (xch) *(uint4*)(s_x + q * kB1DP + c8) = vx[i];
+    }
+    if (g.s) dgam += (double)(g.scale * vsg) * (double)vs;
+    __syncthreads();
+    if (st + (int)gridDim.x < stages) issue(st + gridDim.x);
+#pragma unroll
+    for (int ks = 0; ks < kB1P / 32; ++ks) {
+      bf16x8_t af[4], bf[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bf16_t* a = td + ks * 32 * kB1DP + i * 16;
+        const bf16_t* b = tx + ks * 32 * kB1DP + i * 16;
+        af[i] = tr_frag(a, a + 4 * kB1DP);
+        bf[i] = tr_frag(b, b + 4 * kB1DP);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (wm * 64 + i * 16 >= cout) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (wn * 64 + j * 16 < cin8)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
+        if (wn == 0) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], ones, accb[i], 0, 0, 0);
+      }
+    }
+    if (!g.dx) continue;
+    uint2 res[8];
+    {
+      f32x4_t ad[8];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) ad[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < kB1C / 32; ++ks) {
+        if (ks >= nks) break;
+        const bf16x8_t bf = *(const bf16x8_t*)(drow + ks * 32 + (lane >> 4) * 8);
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+          if (m * 16 < cin8)
+            ad[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8_t*)(wrow + m * 16 * kB1WP + ks * 32), bf,
+                                                            ad[m], 0, 0, 0);
+      }
+      // lane holds dx[pixel 16 wv + (lane & 15)][ci = 16 m + 4 (lane >> 4) + j]
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const uint2 xv = *(const uint2*)(xrow + m * 16 + 4 * (lane >> 4));
+        const float o[4] = {bf2f((bf16_t)(xv.x & 0xffff)), bf2f((bf16_t)(xv.x >> 16)), bf2f((bf16_t)(xv.y & 0xffff)),
+                            bf2f((bf16_t)(xv.y >> 16))};
+        bf16_t r[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          r[j] = f2bf(ad[m][j]);
+          if (g.act == kActRelu) r[j] = o[j] > 0.f ? r[j] : (bf16_t)0;
+          else if (g.act == kActTanh) r[j] = f2bf(bf2f(r[j]) * (1.f - o[j] * o[j]));
+        }
+        res[m] = make_uint2((uint32_t)r[0] | ((uint32_t)r[1] << 16), (uint32_t)r[2] | ((uint32_t)r[3] << 16));
+      }
+    }
+    __syncthreads();  // every wave is done with d
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+      if (m * 16 < cin8) *(uint2*)(drow + m * 16 + 4 * (lane >> 4)) = res[m];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = pl + 16 * i;
+      if (xch && q < np) *(uint4*)(g.dx + (p0 + q) * cin8 + c8) = *(const uint4*)(s_d + q * kB1DP + c8);
+    }
+    if (cin8 > cout) {
+      // d's columns past cout are zero again before the next stage's products
+      __syncthreads();
+      for (int u = tid; u < kB1P * ((cin8 - cout) / 8); u += 256) {
+        const int w = (cin8 - cout) / 8, r = u / w;
+        *(uint4*)(s_d + r * kB1DP + cout + (u - r * w) * 8) = make_uint4(0, 0, 0, 0);
+      }
+    }
+  }
+  // lane holds dW[co = 64 wm + 16 i + 4 (lane >> 4) + q][ci = 64 wn + 16 j + (lane & 15)]
+  const int64_t len = (int64_t)cout * g.cin + cout;
+  float* ps = part + (int64_t)blockIdx.x * len;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int co = wm * 64 + i * 16 + 4 * (lane >> 4) + q;
+      if (co >= cout) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int ci = wn * 64 + j * 16 + (lane & 15);
+        if (ci < g.cin) ps[(int64_t)co * g.cin + ci] = acc[i][j][q];
+      }
+      if (wn == 0 && (lane & 15) == 0) ps[len - cout + co] = accb[i][q];
+    }
+  if (g.s) {
+    dgam = block_sum(dgam, lds);
+    if (tid == 0) g.gpart[blockIdx.x] = (float)dgam;
+  }
+}
+
 // out[k] = scale * sum_b part[b][k] (fixed order, FP64 accumulation). A
 // workgroup handles 32 consecutive k; its 8 thread groups sum the rows
 // g, g + 8, ... and the 8 group sums are added in order.
@@ -338,8 +555,12 @@ __global__ __launch_bounds__(256) void k_reduce_rows(const float* __restrict__ p
 // Bias gradient partials: part[b][c] = sum over workgroup b's pixels of d[p][c].
 // Thread t reads 8 channels (c8 = t % (C/8)) of the pixels of phase t / (C/8);
 // the phases are summed in LDS in a fixed order. Requires C % 8 == 0, C <= 2048.
+// With gamma, d holds a factor S of the DeepONet contraction and the summed
+// gradient is bf16(gamma (scale dy) S).
 __global__ __launch_bounds__(256) void k_bias_grad(const bf16_t* __restrict__ d, int64_t npix, int pitch, int off,
-                                                   int C, float* __restrict__ part) {
+                                                   int C, const float* __restrict__ gamma,
+                                                   const float* __restrict__ dy, float scale,
+                                                   float* __restrict__ part) {
   __shared__ float red[256 * 8];
   const int c8n = C / 8;
   const int G = 256 / c8n;  // pixel phases per workgroup
@@ -355,6 +576,7 @@ __global__ __launch_bounds__(256) void k_bias_grad(const bf16_t* __restrict__ d,
       for (int u = 0; u < 4; ++u) {
         const int64_t pu = p + u * step;
         v[u] = pu < npix ? *(const uint4*)(d + pu * pitch + off + c8 * 8) : make_uint4(0, 0, 0, 0);
+        if (gamma && pu < npix) v[u] = scale8(v[u], gamma[0] * (scale * dy[pu]));
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -709,7 +931,8 @@ __global__ void k_trunk_input(int H, int W, const float* __restrict__ tin, int64
   for (int c = 2; c < 8; ++c) o[c] = 0;
 }
 
-// DeepONet contraction y = gamma * sum_k B_k T_k (FP32 sum of BF16 operands).
+// DeepONet contraction s = sum_k B_k T_k (FP32 sum of BF16 operands) and
+// y = gamma s; s is kept for gamma's gradient.
 // 16 lanes per pixel, 8 basis terms per lane per pass (P % 8 == 0).
 __device__ __forceinline__ float dot8(uint4 a, uint4 b) {
   const uint32_t x[4] = {a.x, a.y, a.z, a.w}, y[4] = {b.x, b.y, b.z, b.w};
@@ -729,64 +952,34 @@ __device__ __forceinline__ float sum16(float v) {
 
 __global__ __launch_bounds__(256) void k_don_fwd(int64_t n, int P, const bf16_t* __restrict__ B,
                                                  const bf16_t* __restrict__ T, const float* __restrict__ gamma,
-                                                 float* __restrict__ y) {
+                                                 float* __restrict__ y, float* __restrict__ sum) {
   const int64_t p = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   const int l = threadIdx.x & 15;
   float s = 0.f;
   if (p < n)
     for (int k = l * 8; k < P; k += 128) s += dot8(*(const uint4*)(B + p * P + k), *(const uint4*)(T + p * P + k));
   s = sum16(s);
-  if (p < n && l == 0) y[p] = gamma[0] * s;
+  if (p < n && l == 0) {
+    sum[p] = s;
+    y[p] = gamma[0] * s;
+  }
 }
 
-__device__ __forceinline__ uint4 scale8(uint4 a, float c) {
-  const uint32_t x[4] = {a.x, a.y, a.z, a.w};
-  uint32_t o[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    o[e] = (uint32_t)f2bf(c * bf2f((bf16_t)(x[e] & 0xffff))) | ((uint32_t)f2bf(c * bf2f((bf16_t)(x[e] >> 16))) << 16);
-  return make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// Its backward for dy = scale * g: dB = gamma dy T, dT = gamma dy B, and
-// per-workgroup partials of dgamma = sum dy sum_k B_k T_k.
-__global__ __launch_bounds__(256) void k_don_bwd(int64_t n, int P, const bf16_t* __restrict__ B,
-                                                 const bf16_t* __restrict__ T, const float* __restrict__ gamma,
-                                                 const float* __restrict__ g, float scale, bf16_t* __restrict__ dB,
-                                                 bf16_t* __restrict__ dT, float* __restrict__ part) {
+// The head's output gradient dB = bf16(gamma (scale g) T) as an array, and
+// per-workgroup shares of gamma's gradient, for heads too wide for k_bwd1x1.
+__global__ __launch_bounds__(256) void k_don_grad(int64_t n, int P, const bf16_t* __restrict__ T,
+                                                  const float* __restrict__ gamma, const float* __restrict__ g,
+                                                  float scale, const float* __restrict__ sum, bf16_t* __restrict__ dB,
+                                                  float* __restrict__ part) {
   __shared__ double lds[kWaves];
-  const int l = threadIdx.x & 15;
+  const int P8 = P / 8;
   const float gam = gamma[0];
   double acc = 0.0;
-  // four pixels per pass, their loads issued together; 16 lanes per pixel,
-  // lane l holding basis terms 8l .. 8l+7 (P <= 128: at most one group)
-  const int k = l * 8;
-  const bool kin = k < P;
-  const int64_t step = (int64_t)gridDim.x * 16;
-  for (int64_t p0 = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); p0 < n; p0 += 4 * step) {
-    uint4 b[4], t[4];
-    float dy[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t p = p0 + u * step;
-      const bool ok = p < n && kin;
-      b[u] = ok ? *(const uint4*)(B + p * P + k) : make_uint4(0, 0, 0, 0);
-      t[u] = ok ? *(const uint4*)(T + p * P + k) : make_uint4(0, 0, 0, 0);
-      dy[u] = p < n ? scale * g[p] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t p = p0 + u * step;
-      const float tot = sum16(dot8(b[u], t[u]));  // all 16 lanes of the pixel take part
-      if (p < n) {
-        const float gd = gam * dy[u];
-        if (kin) {
-          *(uint4*)(dB + p * P + k) = scale8(t[u], gd);
-          *(uint4*)(dT + p * P + k) = scale8(b[u], gd);
-        }
-        if (l == 0) acc += (double)dy[u] * (double)tot;
-      }
-    }
+  for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n * P8; u += (int64_t)gridDim.x * 256) {
+    const int64_t p = u / P8;
+    const float dy = scale * g[p];
+    *(uint4*)(dB + u * 8) = scale8(*(const uint4*)(T + u * 8), gam * dy);
+    if (u == p * P8) acc += (double)dy * (double)sum[p];
   }
   acc = block_sum(acc, lds);
   if (threadIdx.x == 0) part[blockIdx.x] = (float)acc;
@@ -951,6 +1144,17 @@ void launch_wgrad1(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, float* 
   k_wgrad1<<<grid1, 256, 0, s>>>(g, dp, x, part);
 }
 
+bool bwd1x1_fits(int cout, int cin8) { return cout <= kB1C && cin8 <= kB1C; }
+
+// One split per workgroup: 1024 at most (two rounds of the resident
+// workgroups), one per 128-pixel tile where there are fewer.
+int launch_bwd1x1(const Bwd1x1& g, int64_t tiles, float* part, int64_t cap, hipStream_t s) {
+  const int64_t len = (int64_t)g.cout * g.cin + g.cout;
+  const int64_t n = std::max<int64_t>(1, std::min<int64_t>({1024, tiles, cap / len}));
+  k_bwd1x1<<<(unsigned)n, 256, 0, s>>>(g, part);
+  return (int)n;
+}
+
 // Splits and channel tiles of k_wgrad9. Splits: 1024 / (32 x 32 channel tiles of
 // the layer), at most one per pixel tile, and as many rows as the partials
 // buffer holds. Per workgroup 64, 32 or 16 input channels, the widest that pads
@@ -991,9 +1195,9 @@ void launch_reduce_rows(const float* part, int nparts, int64_t len, float scale,
   k_reduce_rows<<<(unsigned)((len + 31) / 32), 256, 0, s>>>(part, nparts, len, scale, out);
 }
 
-void launch_bias_grad(const bf16_t* d, int64_t npix, int pitch, int off, int C, float* part, int nparts,
-                      hipStream_t s) {
-  k_bias_grad<<<nparts, 256, 0, s>>>(d, npix, pitch, off, C, part);
+void launch_bias_grad(const bf16_t* d, int64_t npix, int pitch, int off, int C, const float* gamma, const float* dy,
+                      float scale, float* part, int nparts, hipStream_t s) {
+  k_bias_grad<<<nparts, 256, 0, s>>>(d, npix, pitch, off, C, gamma, dy, scale, part);
 }
 
 void launch_act_bwd(bf16_t* d, int dpitch, const bf16_t* out, int opitch, int ooff, int C, int64_t npix, int mode,
@@ -1079,13 +1283,14 @@ void launch_trunk_input(int H, int W, const float* tin, int64_t t_stride, bf16_t
   k_trunk_input<<<dim3(nblk((int64_t)H * W), nb), 256, 0, s>>>(H, W, tin, t_stride, out);
 }
 
-void launch_don_fwd(int64_t n, int P, const bf16_t* B, const bf16_t* T, const float* gamma, float* y, hipStream_t s) {
-  k_don_fwd<<<(unsigned)((n + 15) / 16), 256, 0, s>>>(n, P, B, T, gamma, y);
+void launch_don_fwd(int64_t n, int P, const bf16_t* B, const bf16_t* T, const float* gamma, float* y, float* sum,
+                    hipStream_t s) {
+  k_don_fwd<<<(unsigned)((n + 15) / 16), 256, 0, s>>>(n, P, B, T, gamma, y, sum);
 }
 
-void launch_don_bwd(int64_t n, int P, const bf16_t* B, const bf16_t* T, const float* gamma, const float* g,
-                    float scale, bf16_t* dB, bf16_t* dT, float* part, int nparts, hipStream_t s) {
-  k_don_bwd<<<nparts, 256, 0, s>>>(n, P, B, T, gamma, g, scale, dB, dT, part);
+void launch_don_grad(int64_t n, int P, const bf16_t* T, const float* gamma, const float* g, float scale,
+                     const float* sum, bf16_t* dB, float* part, int nparts, hipStream_t s) {
+  k_don_grad<<<nparts, 256, 0, s>>>(n, P, T, gamma, g, scale, sum, dB, part);
 }
 
 void launch_loss(int64_t n, const float* R, const float* Ay, float* res, double* part, int nparts, hipStream_t s) {

@@ -20,9 +20,31 @@ void launch_wgrad1(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, float* 
 // ([cout][cin][9] | [cout] each, at most cap floats in all); returns their number.
 int launch_wgrad9(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf16_t* eta, float* part, int64_t cap,
                   hipStream_t s);
+// Backward of a 1x1 layer over nb samples of hw pixels: d [nb][hw][cout], x
+// [nb][hw][cin8] its input, wT the packed transposed weights (Kp values per input
+// channel), dx [nb][hw][cin8] the gradient of the input before its activation act
+// (1 ReLU, 2 tanh, 0 none), or NULL. With gamma: d holds the other factor S of
+// the DeepONet contraction and the gradient is bf16(gamma (scale dy) S).
+// With s: gpart gets one share of gamma's gradient, sum (scale dy) s, per workgroup.
+struct Bwd1x1 {
+  int hw, nb;
+  int cout, cin, cin8;
+  const bf16_t* d;
+  const bf16_t* x;
+  const bf16_t* wT;
+  int Kp, act;
+  bf16_t* dx;
+  const float *gamma, *dy, *s;
+  float scale;
+  float* gpart;
+};
+bool bwd1x1_fits(int cout, int cin8);
+// Partial rows [cout][cin] | [cout] of the weight and bias gradients (at most
+// cap floats, 1024 rows and `tiles` rows); returns their number.
+int launch_bwd1x1(const Bwd1x1& g, int64_t tiles, float* part, int64_t cap, hipStream_t s);
 void launch_reduce_rows(const float* part, int nparts, int64_t len, float scale, float* out, hipStream_t s);
-void launch_bias_grad(const bf16_t* d, int64_t npix, int pitch, int off, int C, float* part, int nparts,
-                      hipStream_t s);
+void launch_bias_grad(const bf16_t* d, int64_t npix, int pitch, int off, int C, const float* gamma, const float* dy,
+                      float scale, float* part, int nparts, hipStream_t s);
 void launch_act_bwd(bf16_t* d, int dpitch, const bf16_t* out, int opitch, int ooff, int C, int64_t npix, int mode,
                     hipStream_t s);
 void launch_copy_ch(const bf16_t* src, int spitch, int soff, bf16_t* dst, int dpitch, int C, int64_t npix, int acc,
@@ -45,9 +67,12 @@ void launch_fill_static_multi(int H, int W, int pitch, int coff, const float* lv
                               const uint8_t* const* masks, int moff, bf16_t* buf, int64_t bstride, int nb,
                               hipStream_t s);
 void launch_trunk_input(int H, int W, const float* tin, int64_t t_stride, bf16_t* out, int nb, hipStream_t s);
-void launch_don_fwd(int64_t n, int P, const bf16_t* B, const bf16_t* T, const float* gamma, float* y, hipStream_t s);
-void launch_don_bwd(int64_t n, int P, const bf16_t* B, const bf16_t* T, const float* gamma, const float* g,
-                    float scale, bf16_t* dB, bf16_t* dT, float* part, int nparts, hipStream_t s);
+// y = gamma s and s = sum_k B_k T_k per pixel.
+void launch_don_fwd(int64_t n, int P, const bf16_t* B, const bf16_t* T, const float* gamma, float* y, float* sum,
+                    hipStream_t s);
+// dB = bf16(gamma (scale g) T) and nparts shares of gamma's gradient.
+void launch_don_grad(int64_t n, int P, const bf16_t* T, const float* gamma, const float* g, float scale,
+                     const float* sum, bf16_t* dB, float* part, int nparts, hipStream_t s);
 void launch_loss(int64_t n, const float* R, const float* Ay, float* res, double* part, int nparts, hipStream_t s);
 void launch_sum_parts(const double* part, int n, double scale, double* out, hipStream_t s);
 // Supervised loss (scale- and shift-invariant misfit of y against the FP64
