@@ -42,6 +42,7 @@ struct TrainState {
   int64_t g_in[kMaxLevels] = {}, g_a[kMaxLevels] = {}, g_cat[kMaxLevels] = {}, g_c[kMaxLevels] = {},
           g_d[kMaxLevels] = {}, g_E[kMaxLevels] = {}, g_Uc[kMaxLevels] = {}, g_bot = 0, g_B = 0,
           g_h[9] = {};
+  float* se = nullptr;  // dEta per node, laid out as eta (one local weight per node)
   int64_t e_a[kMaxLevels] = {}, e_b[kMaxLevels] = {}, e_c[kMaxLevels] = {}, e_d[kMaxLevels] = {};
   // packed BF16 weights for this step: transposed (input gradients) per layer,
   // and the forward packs of the head and trunk layers
@@ -54,6 +55,7 @@ struct TrainState {
   float* f32 = nullptr;  // y, Ay, res, gAy, y / gamma: [5][nb][N]
   float* part = nullptr;
   int64_t part_len = 0;
+  float* rpart = nullptr;  // partial rows that one launch sums at the end: biases, local weights, gamma
   double* dpart = nullptr;  // [nb][kRedBlocks] input-scale partials, then loss partials and the loss value
   // generated right-hand sides (R == NULL)
   GenWs gen;
@@ -82,9 +84,11 @@ void net_train_free(ppe_net* n) {
   dev_free(t->act);
   dev_free(t->grad);
   dev_free(t->eta);
+  dev_free(t->se);
   dev_free(t->packs);
   dev_free(t->f32);
   dev_free(t->part);
+  dev_free(t->rpart);
   dev_free(t->dpart);
   delete t;
   n->train = nullptr;
@@ -189,17 +193,23 @@ static ppe_status train_state(ppe_net* n, int nb, int nx, int ny) {
     t->pT_tr[k] = pk(cin8, t->kT_tr[k]);
   }
   const int64_t N = (int64_t)nx * ny;
-  t->part_len = (int64_t)17 << 20;  // floats: 1024 rows of a 128 x 128 layer
+  t->part_len = (int64_t)16 << 20;  // floats
   t->act = (bf16_t*)dev_alloc(ao * sizeof(bf16_t));
   t->grad = (bf16_t*)dev_alloc(go * sizeof(bf16_t));
   t->eta = cfg.use_eta ? (bf16_t*)dev_alloc(eo * sizeof(bf16_t)) : nullptr;
+  t->se = cfg.use_eta == 2 ? (float*)dev_alloc(eo * sizeof(float)) : nullptr;
   t->packs = (bf16_t*)dev_alloc(po * sizeof(bf16_t));
   t->f32 = (float*)dev_alloc(5 * N * nb * sizeof(float));
   t->part = (float*)dev_alloc(t->part_len * sizeof(float));
+  // biases of every layer, one row of the widest local-weight network per Mesh-Conv, gamma
+  int64_t biases = P + (int64_t)cfg.trunk_hidden * TWd + P;
+  for (int l = 0; l < L; ++l) biases += (l < L - 1 ? 5 : 2) * (int64_t)ch(l);
+  t->rpart = (float*)dev_alloc((kBiasParts * biases + (int64_t)kPhiParts * (6 * cfg.phi_hidden + 1) * 4 * L +
+                                kGammaParts) * sizeof(float));
   t->dpart = (double*)dev_alloc(((size_t)kRedBlocks * (nb + 1) + 8) * sizeof(double));
   t->d_coefs = (Coef*)dev_alloc(nb * sizeof(Coef));
   t->d_masks = (const uint8_t**)dev_alloc(nb * sizeof(void*));
-  if (!t->act || !t->grad || (cfg.use_eta && !t->eta) || !t->packs || !t->f32 || !t->part || !t->dpart ||
+  if (!t->act || !t->grad || (cfg.use_eta && !t->eta) || (cfg.use_eta == 2 && !t->se) || !t->packs || !t->f32 || !t->part || !t->rpart || !t->dpart ||
       !t->d_coefs || !t->d_masks)
     return set_error(PPE_ERR_HIP, "allocation of the training workspace failed");
   HIPCHK(hipMemset(t->act, 0, ao * sizeof(bf16_t)));
@@ -359,12 +369,15 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
                                  Ab + t->o_cat[l], hw(l) * t->p_cat[l], nb, s);
     }
     launch_trunk_input(ny, nx, t->d_lv + t->tin_off, t->lv_stride, Ab + t->o_t0, nb, s);
+    PhiArgs ph{};  // the layers with one local weight per node
     auto eta_fwd = [&](const MConvL& m, int64_t off) {
       const int l = m.level;
-      // one weight per node: the same kernel with Phi's single output
-      const int k = per_node ? 1 : m.cin, k8 = per_node ? 1 : m.cin8;
-      launch_eta_multi(t->H[l], t->W[l], k, k8, HID, t->d_lv + t->lv_off[l], t->lv_stride, W + m.oW1, W + m.ob1,
-                       W + m.oW2, W + m.ob2, E + off, hw(l) * k8, nb, s);
+      if (per_node) {
+        ph.layer[ph.n++] = PhiLayer{t->H[l], t->W[l], t->lv_off[l], m.oW1, off, 0, 0};
+        return;
+      }
+      launch_eta_multi(t->H[l], t->W[l], m.cin, m.cin8, HID, t->d_lv + t->lv_off[l], t->lv_stride, W + m.oW1,
+                       W + m.ob1, W + m.oW2, W + m.ob2, E + off, hw(l) * m.cin8, nb, s);
     };
     if (cfg.use_eta)
       for (int l = 0; l < L; ++l) {
@@ -375,6 +388,16 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
           eta_fwd(n->dec_d[l], t->e_d[l]);
         }
       }
+    if (per_node) {
+      ph.nb = nb;
+      ph.hid = HID;
+      ph.lv = t->d_lv;
+      ph.lv_stride = t->lv_stride;
+      ph.params = W;
+      ph.eta = E;
+      ph.se = t->se;
+      launch_eta_nodes(ph, s);
+    }
     auto etap = [&](int64_t off) -> const bf16_t* { return cfg.use_eta ? E + off : nullptr; };
     auto geo = [&](int l, int cin8, int cout, int y_pitch, int y_off, int act) {
       ConvGeo g{};
@@ -484,64 +507,96 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       g.dp_bstride = hw(l) * dp_pitch;
       g.e_bstride = hw(l) * (per_node ? 1 : cin8);
       g.eta_node = per_node;
-      if (taps == 9) {  // the bias follows the weights in the parameter vector
-        const int rows = launch_wgrad9(g, dp, x, eta, part, cap, s);
-        launch_reduce_rows(part, rows, (int64_t)cout * cin * 9 + cout, 1.f, dG + oW, s);
+      int ns;
+      if (taps == 9) {
+        ns = launch_wgrad9(g, dp, x, eta, part, cap, s);
       } else {
-        const int ns = wgrad_splits(cout, cin8, tiles_of(l), cap);
+        ns = wgrad_splits(cout, cin8, tiles_of(l), cap);
         launch_wgrad1(g, dp, x, part, ns, s);
-        launch_reduce_rows(part, ns, (int64_t)cout * cin, 1.f, dG + oW, s);
       }
+      launch_reduce_rows(part, ns, (int64_t)cout * cin * taps, 1.f, dG + oW, s);
     };
-    auto bias = [&](int l, const bf16_t* d, int pitch, int C, int64_t ob) {
-      launch_bias_grad(d, hw(l) * nb, pitch, 0, C, nullptr, nullptr, 0.f, part, 1024, s);
-      launch_reduce_rows(part, 1024, C, 1.f, dG + ob, s);
+    // bias gradients: partial rows now, their sums in one launch at the end. A
+    // bias nearly cancels where the gradients sum to zero (the head's), so these sums keep
+    // short FP32 chains of their own
+    RowTable rows{};
+    float* rnext = t->rpart;
+    auto bias_rows = [&](int C, int64_t ob) {
+      float* p = rnext;
+      rnext += (int64_t)kBiasParts * C;
+      rows.row[rows.n++] = RowSum{p, kBiasParts, C, dG + ob};
+      return p;
+    };
+    auto bias = [&](int l, const bf16_t* d, int C, int64_t ob, const float* gamma, const float* dy, float scale) {
+      launch_bias_grad(d, hw(l) * nb, C, 0, C, gamma, dy, scale, bias_rows(C, ob), kBiasParts, s);
     };
     auto dgrad = [&](int taps, int l, const bf16_t* dp, int cout_fwd, int64_t pT, int kT, int rows, bf16_t* out) {
       ConvGeo g = geo(l, cout_fwd, rows, rows, 0, 0);
       launch_conv(taps, false, g, nb, dp, nullptr, PK + pT, kT, nullptr, out, s);
     };
-    auto eta_bwd = [&](const MConvL& m, const bf16_t* x, int64_t eoff, bf16_t* dxb) {
-      if (!cfg.use_eta) return;
+    // dX of a Mesh-Conv layer from dXbar (in place), with its local weights'
+    // gradients; skip: the channels [skip_lo, skip_hi) of dX go there instead;
+    // ob >= 0: X is the ReLU output of the layer whose bias lies at ob: dX goes
+    // through the ReLU, and that bias's gradient is formed
+    auto eta_bwd = [&](const MConvL& m, const bf16_t* x, int64_t eoff, bf16_t* dxb, int64_t ob, bf16_t* skip,
+                       int skip_lo, int skip_hi) {
       const int l = m.level;
-      const int len = per_node ? eta_bwd_node_len(HID) : eta_bwd_len(m.cin, HID);
-      // partial rows: up to 2048, as many as the partials buffer holds
-      int np = (int)std::min<int64_t>(2048, cap / len);
-      if (per_node) {
-        np = (int)std::min<int64_t>(np, (hw(l) * nb + 255) / 256);
-        launch_eta_bwd_node(t->H[l], t->W[l], m.cin8, HID, nb, t->d_lv + t->lv_off[l], t->lv_stride, W + m.oW1,
-                            W + m.ob1, W + m.oW2, W + m.ob2, x, E + eoff, dxb, part, np, s);
-      } else {
-        launch_eta_bwd(t->H[l], t->W[l], m.cin, m.cin8, HID, nb, t->d_lv + t->lv_off[l], t->lv_stride, W + m.oW1,
-                       W + m.ob1, W + m.oW2, W + m.ob2, x, E + eoff, hw(l) * m.cin8, dxb, part, np, s);
+      const bool relu = ob >= 0;
+      if (cfg.use_eta != 1) {
+        if (!cfg.use_eta && !relu && !skip) return;
+        EtaDx a{};
+        a.npix = hw(l) * nb;
+        a.cin8 = m.cin8;
+        a.x = x;
+        a.eta = etap(eoff);
+        a.dxb = dxb;
+        a.mask = relu;
+        a.skip = skip;
+        a.skip_lo = skip_lo;
+        a.skip_hi = skip_hi;
+        a.se = cfg.use_eta ? t->se + eoff : nullptr;
+        const bool fused = relu && eta_dx_can_bias(m.cin8);
+        a.bias = fused ? bias_rows(m.cin8, ob) : nullptr;
+        launch_eta_dx(a, s);
+        if (relu && !fused) bias(l, dxb, m.cin8, ob, nullptr, nullptr, 0.f);
+        return;
       }
+      const int len = eta_bwd_len(m.cin, HID);
+      // partial rows: up to 2048, as many as the partials buffer holds
+      const int np = (int)std::min<int64_t>(2048, cap / len);
+      launch_eta_bwd(t->H[l], t->W[l], m.cin, m.cin8, HID, nb, t->d_lv + t->lv_off[l], t->lv_stride, W + m.oW1,
+                     W + m.ob1, W + m.oW2, W + m.ob2, x, E + eoff, hw(l) * m.cin8, dxb, part, np, s);
       launch_reduce_rows(part, np, len, 1.f, dG + m.oW1, s);
+      if (relu) {
+        launch_act_bwd(dxb, m.cin8, x, m.cin8, 0, m.cin8, hw(l) * nb, 1, s);
+        bias(l, dxb, m.cin8, ob, nullptr, nullptr, 0.f);
+      }
+      if (skip) launch_copy_ch(dxb, m.cin8, skip_lo, skip, skip_hi - skip_lo, skip_hi - skip_lo, hw(l) * nb, s);
     };
-    // whole backward of a 1x1 layer where it fits one pass, else its parts
+    // backward of a 1x1 layer: in one pass where it fits, else its parts; the
+    // bias follows the weights in the parameter vector
     auto bwd1 = [&](int l, Bwd1x1 b, int64_t oW) {
       b.hw = (int)hw(l);
       b.nb = nb;
+      bias(l, b.d, b.cout, oW + (int64_t)b.cout * b.cin, b.gamma, b.dy, b.scale);
       if (bwd1x1_fits(b.cout, b.cin8)) {
-        const int64_t room = cap - 1024;  // the last 1024 floats: gamma's shares
-        b.gpart = part + room;
-        const int rows = launch_bwd1x1(b, tiles_of(l), part, room, s);
-        launch_reduce_rows(part, rows, (int64_t)b.cout * b.cin + b.cout, 1.f, dG + oW, s);
-        if (b.s) launch_reduce_rows(b.gpart, rows, 1, 1.f, dG + n->o_gamma, s);
+        const int n1 = launch_bwd1x1(b, tiles_of(l), part, cap, s);
+        launch_reduce_rows(part, n1, (int64_t)b.cout * b.cin, 1.f, dG + oW, s);
         return;
       }
-      bf16_t* dd = const_cast<bf16_t*>(b.d);
       if (b.gamma) {
-        dd = G + t->g_B;
-        launch_don_grad(hw(l) * nb, b.cout, b.d, b.gamma, b.dy, b.scale, b.s, dd, part, 2048, s);
-        launch_reduce_rows(part, 2048, 1, 1.f, dG + n->o_gamma, s);
+        launch_don_grad(hw(l) * nb, b.cout, b.d, b.gamma, b.dy, b.scale, G + t->g_B, s);
+        b.d = G + t->g_B;
       }
-      wgrad(1, l, dd, b.cout, b.cout, b.x, b.cin8, b.cin, nullptr, oW);
-      bias(l, dd, b.cout, b.cout, oW + (int64_t)b.cout * b.cin);
+      wgrad(1, l, b.d, b.cout, b.cout, b.x, b.cin8, b.cin, nullptr, oW);
       if (!b.dx) return;
       ConvGeo g = geo(l, b.cout, b.cin8, b.cin8, 0, 0);
-      launch_conv(1, false, g, nb, dd, nullptr, b.wT, b.Kp, nullptr, b.dx, s);
+      launch_conv(1, false, g, nb, b.d, nullptr, b.wT, b.Kp, nullptr, b.dx, s);
       if (b.act) launch_act_bwd(b.dx, b.cin8, b.x, b.cin8, 0, b.cin8, hw(l) * nb, b.act, s);
     };
+    launch_gamma_grad(N * nb, gAy, dscale, ysum, rnext, s);
+    rows.row[rows.n++] = RowSum{rnext, kGammaParts, 1, dG + n->o_gamma};
+    rnext += kGammaParts;
     // DeepONet contraction, head and trunk: the gradients of B and T are formed
     // where they are read
     {
@@ -557,12 +612,7 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       b.gamma = W + n->o_gamma;
       b.dy = gAy;
       b.scale = dscale;
-      b.s = ysum;
       bwd1(0, b, n->o_headW);
-      // the head's bias gradient, sum gamma dy T, nearly cancels (sum dy = 0): a
-      // pass of its own with short FP32 chains replaces the one above
-      launch_bias_grad(b.d, N * nb, P, 0, P, b.gamma, b.dy, b.scale, part, 1024, s);
-      launch_reduce_rows(part, 1024, P, 1.f, dG + n->o_headb, s);
     }
     for (int k = TH; k >= 0; --k) {
       Bwd1x1 b{};
@@ -588,14 +638,13 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       const MConvL& mc = n->dec_c[l];
       const UpL& u = n->up[l];
       bf16_t* dD = G + t->g_d[l];
+      bias(l, dD, ch(l), md.ob, nullptr, nullptr, 0.f);
       wgrad(9, l, dD, ch(l), ch(l), Ab + t->o_c[l], md.cin8, md.cin, etap(t->e_d[l]), md.oW);
       dgrad(9, l, dD, ch(l), t->pT_d[l], t->kT_d[l], md.cin8, G + t->g_c[l]);
-      eta_bwd(md, Ab + t->o_c[l], t->e_d[l], G + t->g_c[l]);
-      launch_act_bwd(G + t->g_c[l], ch(l), Ab + t->o_c[l], ch(l), 0, ch(l), hw(l) * nb, 1, s);
+      eta_bwd(md, Ab + t->o_c[l], t->e_d[l], G + t->g_c[l], mc.ob, nullptr, 0, 0);
       wgrad(9, l, G + t->g_c[l], ch(l), ch(l), Ab + t->o_cat[l], mc.cin8, mc.cin, etap(t->e_c[l]), mc.oW);
       dgrad(9, l, G + t->g_c[l], ch(l), t->pT_c[l], t->kT_c[l], mc.cin8, G + t->g_cat[l]);
-      eta_bwd(mc, Ab + t->o_cat[l], t->e_c[l], G + t->g_cat[l]);
-      launch_copy_ch(G + t->g_cat[l], t->p_cat[l], ch(l), G + t->g_E[l], ch(l), ch(l), hw(l) * nb, 0, s);
+      eta_bwd(mc, Ab + t->o_cat[l], t->e_c[l], G + t->g_cat[l], -1, G + t->g_E[l], ch(l), 2 * ch(l));
       launch_up_bwd(t->H[l + 1], t->W[l + 1], ch(l), G + t->g_cat[l], t->p_cat[l], hw(l) * t->p_cat[l],
                     G + t->g_Uc[l], hw(l + 1) * ch(l), nb, s);
       const bf16_t* src = (l == L - 2) ? Ab + t->o_bot : Ab + t->o_d[l + 1];
@@ -615,21 +664,25 @@ extern "C" ppe_status ppe_net_train_step(ppe_net* n, int32_t nb, ppe_problem* co
       const MConvL& mb = n->enc_b[l];
       const MConvL& ma = n->enc_a[l];
       bf16_t* dE = (l == L - 1) ? G + t->g_bot : G + t->g_E[l];
-      if (l < L - 1)
-        launch_act_bwd(dE, ch(l), Ab + t->o_cat[l], t->p_cat[l], ch(l), ch(l), hw(l) * nb, 1, s);
+      bias(l, dE, ch(l), mb.ob, nullptr, nullptr, 0.f);
       wgrad(9, l, dE, ch(l), ch(l), Ab + t->o_a[l], mb.cin8, mb.cin, etap(t->e_b[l]), mb.oW);
       dgrad(9, l, dE, ch(l), t->pT_b[l], t->kT_b[l], mb.cin8, G + t->g_a[l]);
-      eta_bwd(mb, Ab + t->o_a[l], t->e_b[l], G + t->g_a[l]);
-      launch_act_bwd(G + t->g_a[l], ch(l), Ab + t->o_a[l], ch(l), 0, ch(l), hw(l) * nb, 1, s);
+      eta_bwd(mb, Ab + t->o_a[l], t->e_b[l], G + t->g_a[l], ma.ob, nullptr, 0, 0);
       wgrad(9, l, G + t->g_a[l], ch(l), ch(l), Ab + t->o_in[l], ma.cin8, ma.cin, etap(t->e_a[l]), ma.oW);
       if (cfg.use_eta || l > 0) {
         dgrad(9, l, G + t->g_a[l], ch(l), t->pT_a[l], t->kT_a[l], ma.cin8, G + t->g_in[l]);
-        eta_bwd(ma, Ab + t->o_in[l], t->e_a[l], G + t->g_in[l]);
+        eta_bwd(ma, Ab + t->o_in[l], t->e_a[l], G + t->g_in[l], -1, nullptr, 0, 0);
       }
       if (l > 0)
         launch_pool_bwd(t->H[l], t->W[l], ch(l - 1), G + t->g_in[l], t->p_in[l], hw(l) * t->p_in[l],
-                        G + t->g_E[l - 1], hw(l - 1) * ch(l - 1), nb, s);
+                        Ab + t->o_cat[l - 1], t->p_cat[l - 1], ch(l - 1), G + t->g_E[l - 1],
+                        hw(l - 1) * ch(l - 1), nb, s);
     }
+    if (per_node) {
+      ph.part = rnext;
+      launch_phi_grad(ph, dG, rows, s);
+    }
+    launch_reduce_table(rows, s);
     HIPCHK(hipGetLastError());
     return PPE_OK;
   };

@@ -27,21 +27,19 @@ __device__ __forceinline__ bf16x8_t tr_frag(const bf16_t* p0, const bf16_t* p1) 
   return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// Weight and bias gradients of a 3x3 layer:
+// Weight gradient of a 3x3 layer:
 //   dW[co][ci][tap] = sum over pixels p of dPre[p][co] * Xbar[p + off(tap)][ci]
-//   db[co] = sum over pixels of dPre[p][co]
 // with Xbar = eta * X (the layer's weighted input), on MFMA 16x16x32 BF16 with
 // A = dPre^T (M = 16 MT output channels, K = pixels) and B = shifted Xbar (N = 16
 // input channels). A workgroup of CT wavefronts owns 16 MT output and 16 CT
 // input channels, wave w the input channels 16 w .. + 15; one set of B operands
 // (nine shifted reads of the staged 8 x 16 pixel tile, halo included) feeds MT
-// MFMAs per tap. The bias is one more column of B, all ones, for the workgroups
-// of the first input channels. Split z takes the pixel tiles z, z + nsplit, ...
-// of all samples, the next tile's loads in flight during the current one's MFMA
-// loop, and leaves a partial row in the parameters' layout
-// [co][ci < cin][tap] | [co]; k_reduce_rows sums the rows in a fixed order. The
-// workgroups of one split run on one XCD (they read the same pixels). The
-// order of every sum depends on nsplit alone, not on the channel tiles.
+// MFMAs per tap. Split z takes the pixel tiles z, z + nsplit, ... of all
+// samples, the next tile's loads in flight during the current one's MFMA loop,
+// and leaves a partial row in the parameters' layout [co][ci < cin][tap];
+// k_reduce_rows sums the rows in a fixed order. The workgroups of one split run
+// on one XCD (they read the same pixels). The order of every sum depends on
+// nsplit alone, not on the channel tiles.
 //
 // Bound by the matrix cores and LDS reads about equally (26 8-byte reads for 36
 // MFMAs per K-step with MT = 4). An earlier form kept transposed copies of
@@ -76,13 +74,11 @@ __global__ __launch_bounds__(64 * CT) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int per = tiles_x * tiles_y, tiles = per * g.nb;
   const int lane = threadIdx.x & 63, ct = threadIdx.x >> 6;
 
-  f32x4_t acc[9][MT], accb[MT];
+  f32x4_t acc[9][MT];
 #pragma unroll
-  for (int m = 0; m < MT; ++m) {
-    accb[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  }
 
   uint4 vx[NX], vd[ND], ve[ETA == kEtaChannel ? NX : 1];
   uint32_t ve1[ETA == kEtaNode ? NX : 1];
@@ -145,10 +141,6 @@ __global__ __launch_bounds__(64 * CT) __attribute__((amdgpu_waves_per_eu(2))) vo
   const int q = lane >> 4, jr = (lane & 15) >> 2, jc = 4 * (lane & 3);
   const bf16_t* ad = s_d + ((q >> 1) * TW + 8 * (q & 1) + jr) * DP + jc;
   const bf16_t* ax = s_x + ((q >> 1) * LW + 8 * (q & 1) + jr) * XP + ct * 16 + jc;
-  bf16x8_t ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
-  const bool with_bias = ci0 == 0 && ct == 0;
 
   if (split < tiles) issue(split);
   for (int t = split; t < tiles; t += nsplit) {
@@ -170,27 +162,20 @@ __global__ __launch_bounds__(64 * CT) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
         for (int m = 0; m < MT; ++m) acc[tap][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[m], bf, acc[tap][m], 0, 0, 0);
       }
-      if (with_bias) {
-#pragma unroll
-        for (int m = 0; m < MT; ++m) accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[m], ones, accb[m], 0, 0, 0);
-      }
     }
   }
   // lane holds dW[co0 + 16 m + 4 (lane >> 4) + j][ci0 + 16 ct + (lane & 15)] per tap
   const int ci = ci0 + ct * 16 + (lane & 15);
-  const int64_t len = (int64_t)g.cout * g.cin * 9 + g.cout;
-  float* ps = part + (int64_t)split * len;
+  if (ci >= g.cin) return;
+  float* ps = part + (int64_t)split * g.cout * g.cin * 9;
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int co = co0 + m * 16 + 4 * (lane >> 4) + j;
       if (co >= g.cout) continue;
-      if (ci < g.cin) {
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) ps[((int64_t)co * g.cin + ci) * 9 + tap] = acc[tap][m][j];
-      }
-      if (with_bias && (lane & 15) == 0) ps[len - g.cout + co] = accb[m][j];
+      for (int tap = 0; tap < 9; ++tap) ps[((int64_t)co * g.cin + ci) * 9 + tap] = acc[tap][m][j];
     }
 }
 
@@ -306,21 +291,21 @@ __global__ __launch_bounds__(256) void k_wgrad1(WgradGeo g, const bf16_t* __rest
 
 // Whole backward of a 1x1 layer of at most 128 output and input channels (the
 // trunk, the head, the narrow up-convolutions) in one pass over its pixels:
-//   dW[co][ci] = sum_p d[p][co] x[p][ci],  db[co] = sum_p d[p][co],
+//   dW[co][ci] = sum_p d[p][co] x[p][ci],
 //   dx[p][ci]  = act'(x[p][ci]) * bf16(sum_co W[co][ci] d[p][co]),
 // where x is the layer's input and act' the derivative of the activation that
 // made it (1 for ReLU where x > 0, 1 - x^2 for tanh). d is read, or formed
 // from the DeepONet contraction y = gamma sum_k B_k T_k: d = bf16(gamma dy S)
 // with S the other factor (T for the head, B for the trunk output).
 // Stages of 64 pixels: d and x go to LDS as they lie in memory (channels of a
-// pixel together). dW and db take both operands by transposed reads (K = pixels;
+// pixel together). dW takes both operands by transposed reads (K = pixels;
 // wave w the quarter (w / 2, w % 2) of the channel square), dx takes d's rows
 // as they are and the weights from LDS (wave w the pixels 16 w ..); its result
 // replaces d in LDS and leaves as whole 16-byte pieces. The next stage's loads are in flight
 // meanwhile.
 // Bound by HBM: 768 B per pixel at 128 channels (d and x read, dx written) where
-// separate launches for dW, db, dx and act' moved 2 KB. At 4.2 M pixels a
-// 128 x 128 layer takes 870 us against 286 + 205 + 385 + 420.
+// separate launches for dW, dx and act' moved 1.8 KB. At 4.2 M pixels a
+// 128 x 128 layer takes 870 us against 286 + 385 + 420.
 constexpr int kB1P = 64;     // pixels per stage
 constexpr int kB1C = 128;    // channels at most
 constexpr int kB1DP = kB1C + 16;  // LDS pitch (bf16) of a pixel: see k_wgrad9
@@ -341,7 +326,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ __attribute__((aligned(16))) bf16_t s_d[kB1P * kB1DP];
   __shared__ __attribute__((aligned(16))) bf16_t s_x[kB1P * kB1DP];
   __shared__ __attribute__((aligned(16))) bf16_t s_w[kB1C * kB1WP];
-  __shared__ double lds[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int wm = wv >> 1, wn = wv & 1;
   const int cout = g.cout, cin8 = g.cin8;
@@ -361,22 +345,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
           r < cin8 ? *(const uint4*)(g.wT + (int64_t)r * g.Kp + q * 8) : make_uint4(0, 0, 0, 0);
     }
   }
-  f32x4_t acc[4][4], accb[4];
+  f32x4_t acc[4][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    accb[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  }
-  bf16x8_t ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
   // staging: thread t holds the 8-channel group t % 16 of pixels t / 16 + 16 i
   const int c8 = (tid & 15) * 8, pl = tid >> 4;
   const bool dch = c8 < cout, xch = c8 < cin8;
   const float gam = g.gamma ? g.gamma[0] : 0.f;
   uint4 vd[4], vx[4];
-  float vg[4], vs = 0.f, vsg = 0.f;
+  float vg[4];
   int left = 0;  // pixels of the stage in flight
   int64_t pst = 0;  // its first pixel
   auto issue = [&](int st) {
@@ -397,14 +376,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       if (ok && xch) vx[i] = *(const uint4*)(xb + q * cin8);
       if (ok && g.gamma) vg[i] = g.dy[p0 + q];
     }
-    if (g.s && tid < left) {
-      vs = g.s[p0 + tid];
-      vsg = g.dy[p0 + tid];
-    } else {
-      vs = 0.f;
-    }
   };
-  double dgam = 0.0;
   // transposed reads of a K-step of 32 pixels: group lane / 16 holds pixels
   // 8 (lane / 16) .. + 7
   const int jr = (lane & 15) >> 2, jc = 4 * (lane & 3);
@@ -425,7 +397,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       if (dch) *(uint4*)(s_d + q * kB1DP + c8) = g.gamma ? scale8(vd[i], gam * (g.scale * vg[i])) : vd[i];
       if (xch) *(uint4*)(s_x + q * kB1DP + c8) = vx[i];
     }
-    if (g.s) dgam += (double)(g.scale * vsg) * (double)vs;
     __syncthreads();
     if (st + (int)gridDim.x < stages) issue(st + gridDim.x);
 #pragma unroll
@@ -445,7 +416,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         for (int j = 0; j < 4; ++j)
           if (wn * 64 + j * 16 < cin8)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-        if (wn == 0) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], ones, accb[i], 0, 0, 0);
       }
     }
     if (!g.dx) continue;
@@ -500,8 +470,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
   }
   // lane holds dW[co = 64 wm + 16 i + 4 (lane >> 4) + q][ci = 64 wn + 16 j + (lane & 15)]
-  const int64_t len = (int64_t)cout * g.cin + cout;
-  float* ps = part + (int64_t)blockIdx.x * len;
+  float* ps = part + (int64_t)blockIdx.x * cout * g.cin;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -513,12 +482,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         const int ci = wn * 64 + j * 16 + (lane & 15);
         if (ci < g.cin) ps[(int64_t)co * g.cin + ci] = acc[i][j][q];
       }
-      if (wn == 0 && (lane & 15) == 0) ps[len - cout + co] = accb[i][q];
     }
-  if (g.s) {
-    dgam = block_sum(dgam, lds);
-    if (tid == 0) g.gpart[blockIdx.x] = (float)dgam;
-  }
 }
 
 // out[k] = scale * sum_b part[b][k] (fixed order, FP64 accumulation). A
@@ -550,6 +514,38 @@ __global__ __launch_bounds__(256) void k_reduce_rows(const float* __restrict__ p
     for (int q = 0; q < 8; ++q) tot += red[q][kk];
     out[k] = (float)(scale * tot);
   }
+}
+
+// The same sums for several arrays in one launch: blockIdx.y the table's entry.
+__global__ __launch_bounds__(256) void k_reduce_table(RowTable t) {
+  __shared__ double red[8][32];
+  const RowSum& r = t.row[blockIdx.y];
+  if ((int)blockIdx.x * 32 >= r.len) return;
+  const int kk = threadIdx.x & 31, g = threadIdx.x >> 5, k = blockIdx.x * 32 + kk;
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  if (k < r.len) {
+    int b = g;
+    for (; b + 24 < r.nparts; b += 32) {
+      s0 += r.part[(int64_t)b * r.len + k];
+      s1 += r.part[(int64_t)(b + 8) * r.len + k];
+      s2 += r.part[(int64_t)(b + 16) * r.len + k];
+      s3 += r.part[(int64_t)(b + 24) * r.len + k];
+    }
+    for (; b < r.nparts; b += 8) s0 += r.part[(int64_t)b * r.len + k];
+  }
+  red[g][kk] = (s0 + s1) + (s2 + s3);
+  __syncthreads();
+  if (g == 0 && k < r.len) {
+    double tot = 0.0;
+    for (int q = 0; q < 8; ++q) tot += red[q][kk];
+    r.out[k] = (float)tot;
+  }
+}
+
+void launch_reduce_table(const RowTable& t, hipStream_t s) {
+  int len = 1;
+  for (int k = 0; k < t.n; ++k) len = std::max(len, t.row[k].len);
+  k_reduce_table<<<dim3((len + 31) / 32, t.n), 256, 0, s>>>(t);
 }
 
 // Bias gradient partials: part[b][c] = sum over workgroup b's pixels of d[p][c].
@@ -628,48 +624,84 @@ __global__ void k_act_bwd(bf16_t* __restrict__ d, int dpitch, const bf16_t* __re
   *dp = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// dst[p][c] (+)= src[p][soff + c], c < C.
+// dst[p][c] = src[p][soff + c], c < C; eight channels per thread.
 __global__ void k_copy_ch(const bf16_t* __restrict__ src, int spitch, int soff, bf16_t* __restrict__ dst, int dpitch,
-                          int C, int64_t npix, int accumulate) {
+                          int C, int64_t npix) {
+  const int c8n = C / 8;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= npix * C) return;
-  const int64_t p = idx / C;
-  const int c = (int)(idx - p * C);
-  float v = bf2f(src[p * spitch + soff + c]);
-  if (accumulate) v += bf2f(dst[p * dpitch + c]);
-  dst[p * dpitch + c] = f2bf(v);
+  if (idx >= npix * c8n) return;
+  const int64_t p = idx / c8n;
+  const int c = (int)(idx - p * c8n) * 8;
+  *(uint4*)(dst + p * dpitch + c) = *(const uint4*)(src + p * spitch + soff + c);
 }
 
-// Backward of nearest 2x upsampling: coarse[p][c] = sum of the 4 fine pixels.
+// Backward of nearest 2x upsampling: coarse[p][c] = sum of the 4 fine pixels,
+// eight channels per thread (C a multiple of 8).
 __global__ void k_up_bwd(int Hc, int Wc, int C, const bf16_t* __restrict__ fine, int fpitch, int64_t f_bs,
                          bf16_t* __restrict__ coarse, int64_t c_bs) {
+  const int c8n = C / 8;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)Hc * Wc * C) return;
-  const int c = (int)(idx % C);
-  const int64_t p = idx / C;
+  if (idx >= (int64_t)Hc * Wc * c8n) return;
+  const int64_t p = idx / c8n;
+  const int c = (int)(idx - p * c8n) * 8;
   const int y = (int)(p / Wc), xx = (int)(p - (int64_t)y * Wc);
-  const bf16_t* f = fine + blockIdx.y * f_bs;
-  float s = 0.f;
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) s += bf2f(f[((int64_t)(2 * y + a) * 2 * Wc + 2 * xx + b) * fpitch + c]);
-  coarse[blockIdx.y * c_bs + p * C + c] = f2bf(s);
+  const bf16_t* f = fine + blockIdx.y * f_bs + c;
+  uint4 v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    v[q] = *(const uint4*)(f + ((int64_t)(2 * y + (q >> 1)) * 2 * Wc + 2 * xx + (q & 1)) * fpitch);
+  uint32_t o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float lo = 0.f, hi = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t w4[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+      lo += bf2f((bf16_t)(w4[e] & 0xffff));
+      hi += bf2f((bf16_t)(w4[e] >> 16));
+    }
+    o[e] = (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
+  }
+  *(uint4*)(coarse + blockIdx.y * c_bs + p * C + c) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// Backward of 2x2 average pooling: dE[2y+a][2x+b][c] += 0.25 * dpool[y][x][c].
+// Backward of 2x2 average pooling into the features' gradient, and through
+// the features' ReLU: dE = relu'(E) bf16(dE + 0.25 dpool), E the stored
+// features (pitch epitch, channel offset eoff); eight channels per thread.
 __global__ void k_pool_bwd(int Hc, int Wc, int C, const bf16_t* __restrict__ dpool, int ppitch, int64_t p_bs,
-                           bf16_t* __restrict__ dE, int64_t e_bs) {
+                           const bf16_t* __restrict__ E, int epitch, int eoff, bf16_t* __restrict__ dE, int64_t e_bs) {
+  const int c8n = C / 8;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)Hc * Wc * C) return;
-  const int c = (int)(idx % C);
-  const int64_t p = idx / C;
+  if (idx >= (int64_t)Hc * Wc * c8n) return;
+  const int64_t p = idx / c8n;
+  const int c = (int)(idx - p * c8n) * 8;
   const int y = (int)(p / Wc), xx = (int)(p - (int64_t)y * Wc);
-  const float g = 0.25f * bf2f(dpool[blockIdx.y * p_bs + p * ppitch + c]);
-  bf16_t* e = dE + blockIdx.y * e_bs;
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) {
-      bf16_t* q = e + ((int64_t)(2 * y + a) * 2 * Wc + 2 * xx + b) * C + c;
-      *q = f2bf(bf2f(*q) + g);
+  const uint4 gv = *(const uint4*)(dpool + blockIdx.y * p_bs + p * ppitch + c);
+  const uint32_t g4[4] = {gv.x, gv.y, gv.z, gv.w};
+  const int64_t base = (int64_t)blockIdx.y * 4 * Hc * Wc;  // this sample's first fine pixel
+  bf16_t* e = dE + blockIdx.y * e_bs + c;
+  uint4 dv[4], ev[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t f = (int64_t)(2 * y + (q >> 1)) * 2 * Wc + 2 * xx + (q & 1);
+    dv[q] = *(const uint4*)(e + f * C);
+    ev[q] = *(const uint4*)(E + (base + f) * epitch + eoff + c);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t f = (int64_t)(2 * y + (q >> 1)) * 2 * Wc + 2 * xx + (q & 1);
+    const uint32_t d4[4] = {dv[q].x, dv[q].y, dv[q].z, dv[q].w}, e4[4] = {ev[q].x, ev[q].y, ev[q].z, ev[q].w};
+    uint32_t o[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float glo = 0.25f * bf2f((bf16_t)(g4[k] & 0xffff)), ghi = 0.25f * bf2f((bf16_t)(g4[k] >> 16));
+      float lo = bf2f((bf16_t)(d4[k] & 0xffff)) + glo, hi = bf2f((bf16_t)(d4[k] >> 16)) + ghi;
+      lo = bf2f((bf16_t)(e4[k] & 0xffff)) > 0.f ? lo : 0.f;
+      hi = bf2f((bf16_t)(e4[k] >> 16)) > 0.f ? hi : 0.f;
+      o[k] = (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
     }
+    *(uint4*)(e + f * C) = make_uint4(o[0], o[1], o[2], o[3]);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -965,22 +997,25 @@ __global__ __launch_bounds__(256) void k_don_fwd(int64_t n, int P, const bf16_t*
   }
 }
 
-// The head's output gradient dB = bf16(gamma (scale g) T) as an array, and
-// per-workgroup shares of gamma's gradient, for heads too wide for k_bwd1x1.
+// The head's output gradient dB = bf16(gamma (scale g) T) as an array, for
+// heads too wide for k_bwd1x1.
 __global__ __launch_bounds__(256) void k_don_grad(int64_t n, int P, const bf16_t* __restrict__ T,
                                                   const float* __restrict__ gamma, const float* __restrict__ g,
-                                                  float scale, const float* __restrict__ sum, bf16_t* __restrict__ dB,
-                                                  float* __restrict__ part) {
-  __shared__ double lds[kWaves];
+                                                  float scale, bf16_t* __restrict__ dB) {
   const int P8 = P / 8;
   const float gam = gamma[0];
+  for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n * P8; u += (int64_t)gridDim.x * 256)
+    *(uint4*)(dB + u * 8) = scale8(*(const uint4*)(T + u * 8), gam * (scale * g[u / P8]));
+}
+
+// Per-workgroup shares of gamma's gradient, sum of (scale g) s over pixels.
+__global__ __launch_bounds__(256) void k_gamma_grad(int64_t n, const float* __restrict__ g, float scale,
+                                                    const float* __restrict__ sum, float* __restrict__ part) {
+  __shared__ double lds[kWaves];
   double acc = 0.0;
-  for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n * P8; u += (int64_t)gridDim.x * 256) {
-    const int64_t p = u / P8;
-    const float dy = scale * g[p];
-    *(uint4*)(dB + u * 8) = scale8(*(const uint4*)(T + u * 8), gam * dy);
-    if (u == p * P8) acc += (double)dy * (double)sum[p];
-  }
+  if ((threadIdx.x & 15) == 0)
+    for (int64_t p = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); p < n; p += (int64_t)gridDim.x * 16)
+      acc += (double)(scale * g[p]) * (double)sum[p];
   acc = block_sum(acc, lds);
   if (threadIdx.x == 0) part[blockIdx.x] = (float)acc;
 }
@@ -1149,8 +1184,7 @@ bool bwd1x1_fits(int cout, int cin8) { return cout <= kB1C && cin8 <= kB1C; }
 // One split per workgroup: 1024 at most (two rounds of the resident
 // workgroups), one per 128-pixel tile where there are fewer.
 int launch_bwd1x1(const Bwd1x1& g, int64_t tiles, float* part, int64_t cap, hipStream_t s) {
-  const int64_t len = (int64_t)g.cout * g.cin + g.cout;
-  const int64_t n = std::max<int64_t>(1, std::min<int64_t>({1024, tiles, cap / len}));
+  const int64_t n = std::max<int64_t>(1, std::min<int64_t>({1024, tiles, cap / ((int64_t)g.cout * g.cin8)}));
   k_bwd1x1<<<(unsigned)n, 256, 0, s>>>(g, part);
   return (int)n;
 }
@@ -1163,7 +1197,7 @@ int launch_bwd1x1(const Bwd1x1& g, int64_t tiles, float* part, int64_t cap, hipS
 int launch_wgrad9(const WgradGeo& g, const bf16_t* dp, const bf16_t* x, const bf16_t* eta, float* part, int64_t cap,
                   hipStream_t s) {
   const int64_t tiles = (int64_t)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.nb;
-  const int64_t len = (int64_t)g.cout * g.cin * 9 + g.cout;
+  const int64_t len = (int64_t)g.cout * g.cin8 * 9;
   const int64_t blocks32 = (int64_t)((g.cout + 31) / 32) * ((g.cin8 + 31) / 32);
   const int64_t ns =
       std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(1, 1024 / blocks32), tiles, cap / len}));
@@ -1205,19 +1239,20 @@ void launch_act_bwd(bf16_t* d, int dpitch, const bf16_t* out, int opitch, int oo
   k_act_bwd<<<nblk(npix * (C / 8)), 256, 0, s>>>(d, dpitch, out, opitch, ooff, C, npix, mode);
 }
 
-void launch_copy_ch(const bf16_t* src, int spitch, int soff, bf16_t* dst, int dpitch, int C, int64_t npix, int acc,
+void launch_copy_ch(const bf16_t* src, int spitch, int soff, bf16_t* dst, int dpitch, int C, int64_t npix,
                     hipStream_t s) {
-  k_copy_ch<<<nblk(npix * C), 256, 0, s>>>(src, spitch, soff, dst, dpitch, C, npix, acc);
+  k_copy_ch<<<nblk(npix * (C / 8)), 256, 0, s>>>(src, spitch, soff, dst, dpitch, C, npix);
 }
 
 void launch_up_bwd(int Hc, int Wc, int C, const bf16_t* fine, int fpitch, int64_t f_bs, bf16_t* coarse, int64_t c_bs,
                    int nb, hipStream_t s) {
-  k_up_bwd<<<dim3(nblk((int64_t)Hc * Wc * C), nb), 256, 0, s>>>(Hc, Wc, C, fine, fpitch, f_bs, coarse, c_bs);
+  k_up_bwd<<<dim3(nblk((int64_t)Hc * Wc * (C / 8)), nb), 256, 0, s>>>(Hc, Wc, C, fine, fpitch, f_bs, coarse, c_bs);
 }
 
-void launch_pool_bwd(int Hc, int Wc, int C, const bf16_t* dpool, int ppitch, int64_t p_bs, bf16_t* dE, int64_t e_bs,
-                     int nb, hipStream_t s) {
-  k_pool_bwd<<<dim3(nblk((int64_t)Hc * Wc * C), nb), 256, 0, s>>>(Hc, Wc, C, dpool, ppitch, p_bs, dE, e_bs);
+void launch_pool_bwd(int Hc, int Wc, int C, const bf16_t* dpool, int ppitch, int64_t p_bs, const bf16_t* E, int epitch,
+                     int eoff, bf16_t* dE, int64_t e_bs, int nb, hipStream_t s) {
+  k_pool_bwd<<<dim3(nblk((int64_t)Hc * Wc * (C / 8)), nb), 256, 0, s>>>(Hc, Wc, C, dpool, ppitch, p_bs, E, epitch, eoff,
+                                                                        dE, e_bs);
 }
 
 void launch_eta_multi(int H, int W, int cin, int cin8, int hid, const float* lv, int64_t lv_stride, const float* W1,
@@ -1288,9 +1323,13 @@ void launch_don_fwd(int64_t n, int P, const bf16_t* B, const bf16_t* T, const fl
   k_don_fwd<<<(unsigned)((n + 15) / 16), 256, 0, s>>>(n, P, B, T, gamma, y, sum);
 }
 
-void launch_don_grad(int64_t n, int P, const bf16_t* T, const float* gamma, const float* g, float scale,
-                     const float* sum, bf16_t* dB, float* part, int nparts, hipStream_t s) {
-  k_don_grad<<<nparts, 256, 0, s>>>(n, P, T, gamma, g, scale, sum, dB, part);
+void launch_don_grad(int64_t n, int P, const bf16_t* T, const float* gamma, const float* g, float scale, bf16_t* dB,
+                     hipStream_t s) {
+  k_don_grad<<<2048, 256, 0, s>>>(n, P, T, gamma, g, scale, dB);
+}
+
+void launch_gamma_grad(int64_t n, const float* g, float scale, const float* sum, float* part, hipStream_t s) {
+  k_gamma_grad<<<kGammaParts, 256, 0, s>>>(n, g, scale, sum, part);
 }
 
 void launch_loss(int64_t n, const float* R, const float* Ay, float* res, double* part, int nparts, hipStream_t s) {
@@ -1309,108 +1348,288 @@ void launch_anorm_loss(int64_t N, int nb, const float* y, const float* Ay, const
   k_anorm_grad<<<dim3(nparts, nb), 256, 0, s>>>(N, nb, Ay, R, part, nparts, dy, lsamp);
 }
 
-// Mesh-Conv local-weight backward with one local weight per node (Eqs.
-// 17-18 as written: Phi has one output). Given dXbar (gradient of the
-// weighted input) and the layer input X: dX = eta * dXbar (in place of
-// dXbar), dEta[p] = sum_c dXbar[p][c] X[p][c], and through eta = exp(-Phi^2),
-// Phi = W2 . tanh(W1 d + b1) + b2 (d the node's four distances), the
-// gradients of Phi's parameters. One thread per pixel of the batch
-// (grid-stride). Each thread sums its pixels' parameter gradients; a wave
-// adds its lanes by a butterfly and the workgroup its waves in order, into
-// one partial row [W1 (hid*4) | b1 (hid) | W2 (hid) | b2] (the layout of
-// these parameters in the flat vector). HC = hid rounded up to a power of two.
+// Input gradient of a layer with one local weight per node (or none), given
+// g = dXbar, the gradient of the weighted input, and the layer input X:
+//   dX = bf16(eta g), where masked also zero where X <= 0 (X a ReLU output),
+//   se[p] = dEta[p] = sum_c g[p][c] X[p][c].
+// dX replaces g, except that channels [skip_lo, skip_hi) go to the rows of
+// `skip` (the encoder's feature gradient) and later ones nowhere (the static
+// channels of a decoder concatenation). With `bias`, dX is the gradient of the
+// pre-activations of the layer before, and bias[b][c] receives workgroup b's sum
+// over its pixels: that layer's bias gradient, in k_bias_grad's order (the same
+// pixels per thread and workgroup).
+// LP lanes (a power of two, at most 16) share a pixel, lane l taking its
+// 8-channel groups l, l + LP, ...; four pixels per thread in flight. se is one
+// chain over the channels in order: it passes from lane to lane (DPP row
+// shifts), each lane adding its group when its turn comes.
+// Bound by HBM: 6 B per channel and pixel. One thread per pixel, with the
+// parameter gradients in the same kernel, took 4.5 ms for the 14 layers of 64
+// samples of 256 x 256, and separate passes for the mask and the skip channels
+// 3.0 ms more; this and k_phi_grad take 2.1 ms.
+template <int LP>
+__global__ __launch_bounds__(256) void k_eta_dx(EtaDx a) {
+  constexpr int PX = 4;
+  __shared__ float red[256 * 8];
+  const int l = threadIdx.x & (LP - 1);
+  const int G = a.cin8 / 8;
+  const int64_t step = (int64_t)gridDim.x * (256 / LP);
+  float bs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int64_t p0 = (int64_t)blockIdx.x * (256 / LP) + threadIdx.x / LP; p0 < a.npix; p0 += PX * step) {
+    float e[PX], se[PX];
+#pragma unroll
+    for (int u = 0; u < PX; ++u) {
+      const int64_t p = p0 + u * step;
+      e[u] = a.eta && p < a.npix ? bf2f(a.eta[p]) : 1.f;
+      se[u] = 0.f;
+    }
+    for (int c0 = 0; c0 < G; c0 += LP) {  // all lanes of a pixel together
+      const int c8 = c0 + l;
+      uint4 gv[PX], xv[PX];
+#pragma unroll
+      for (int u = 0; u < PX; ++u) {
+        const int64_t p = p0 + u * step;
+        gv[u] = xv[u] = make_uint4(0, 0, 0, 0);
+        if (p < a.npix && c8 < G) {
+          gv[u] = *(const uint4*)(a.dxb + p * a.cin8 + c8 * 8);
+          xv[u] = *(const uint4*)(a.x + p * a.cin8 + c8 * 8);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < PX; ++u) {
+        const int64_t p = p0 + u * step;
+        const uint32_t ga[4] = {gv[u].x, gv[u].y, gv[u].z, gv[u].w}, xa[4] = {xv[u].x, xv[u].y, xv[u].z, xv[u].w};
+        float g[8], x[8];
+        uint32_t o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          g[2 * k] = bf2f((bf16_t)(ga[k] & 0xffff));
+          g[2 * k + 1] = bf2f((bf16_t)(ga[k] >> 16));
+          x[2 * k] = bf2f((bf16_t)(xa[k] & 0xffff));
+          x[2 * k + 1] = bf2f((bf16_t)(xa[k] >> 16));
+        }
+        if (a.se) {
+          // the chain's value enters at lane 0 and leaves at lane LP - 1
+          float v = se[u];
+#pragma unroll
+          for (int r = 0; r < LP; ++r) {
+            float w = v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w += g[2 * k] * x[2 * k] + g[2 * k + 1] * x[2 * k + 1];
+            if (LP == 1) {
+              v = w;
+            } else {
+              v = l == r ? w : v;  // lane r's turn
+              if (r + 1 < LP) {
+                const float from = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x111, 0xf, 0xf, true));
+                v = l == r + 1 ? from : v;
+              }
+            }
+          }
+          se[u] = LP == 1 ? v : __shfl(v, LP - 1, LP);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float d0 = e[u] * g[2 * k], d1 = e[u] * g[2 * k + 1];
+          if (a.mask) {
+            d0 = x[2 * k] > 0.f ? d0 : 0.f;
+            d1 = x[2 * k + 1] > 0.f ? d1 : 0.f;
+          }
+          o[k] = (uint32_t)f2bf(d0) | ((uint32_t)f2bf(d1) << 16);
+        }
+        if (p >= a.npix || c8 >= G) continue;
+        const uint4 d = make_uint4(o[0], o[1], o[2], o[3]);
+        const int c = c8 * 8;
+        if (!a.skip || c < a.skip_lo) *(uint4*)(a.dxb + p * a.cin8 + c) = d;
+        else if (c < a.skip_hi) *(uint4*)(a.skip + p * (a.skip_hi - a.skip_lo) + c - a.skip_lo) = d;
+        if (a.bias) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            bs[2 * k] += bf2f((bf16_t)(o[k] & 0xffff));
+            bs[2 * k + 1] += bf2f((bf16_t)(o[k] >> 16));
+          }
+        }
+      }
+    }
+    if (a.se) {
+#pragma unroll
+      for (int u = 0; u < PX; ++u)
+        if (l == 0 && p0 + u * step < a.npix) a.se[p0 + u * step] = se[u];
+    }
+  }
+  if (!a.bias) return;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[threadIdx.x * 8 + e] = bs[e];
+  __syncthreads();
+  for (int c = threadIdx.x; c < a.cin8; c += 256) {
+    float sum = 0.f;
+    for (int q = 0; q < 256 / LP; ++q) sum += red[(q * LP + c / 8) * 8 + (c % 8)];
+    a.bias[(int64_t)blockIdx.x * a.cin8 + c] = sum;
+  }
+}
+
+// Lanes per pixel: the widest power of two that the 8-channel groups fill once.
+static int eta_dx_lanes(int cin8) {
+  const int G = cin8 / 8;
+  return G >= 16 ? 16 : G >= 8 ? 8 : G >= 4 ? 4 : G >= 2 ? 2 : 1;
+}
+
+bool eta_dx_can_bias(int cin8) { return eta_dx_lanes(cin8) * 8 == cin8; }
+
+void launch_eta_dx(const EtaDx& a, hipStream_t s) {
+  const int lp = eta_dx_lanes(a.cin8);
+  const unsigned n =
+      a.bias ? kBiasParts : (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (a.npix * lp + 1023) / 1024));
+  if (lp == 16) k_eta_dx<16><<<n, 256, 0, s>>>(a);
+  else if (lp == 8) k_eta_dx<8><<<n, 256, 0, s>>>(a);
+  else if (lp == 4) k_eta_dx<4><<<n, 256, 0, s>>>(a);
+  else if (lp == 2) k_eta_dx<2><<<n, 256, 0, s>>>(a);
+  else k_eta_dx<1><<<n, 256, 0, s>>>(a);
+}
+
+// The layer of workgroup b of a launch over several layers, and b's number
+// within the layer's workgroups.
+__device__ __forceinline__ const PhiLayer& phi_layer(const PhiArgs& a, int b, int& w) {
+  int k = 0;
+  while (k + 1 < a.n && a.layer[k + 1].wg0 <= b) ++k;
+  w = b - a.layer[k].wg0;
+  return a.layer[k];
+}
+
+// Local weights (Eq. 17) of all layers with one weight per node, one thread per
+// node: eta = exp(-Phi^2), Phi = W2 . tanh(W1 d + b1) + b2 with d the node's four
+// distances. Bound by the 2 x 16 transcendentals a node. HC = hidden units
+// rounded up to a power of two.
 template <int HC>
-__global__ __launch_bounds__(256) void k_eta_bwd_node(int H, int W, int cin8, int hid, int nb,
-                                                      const float* __restrict__ lv, int64_t lv_stride,
-                                                      const float* __restrict__ W1, const float* __restrict__ b1,
-                                                      const float* __restrict__ W2, const float* __restrict__ b2,
-                                                      const bf16_t* __restrict__ x, const bf16_t* __restrict__ eta,
-                                                      bf16_t* __restrict__ dxb, float* __restrict__ part) {
+__global__ __launch_bounds__(256) void k_eta_nodes(PhiArgs a) {
+  int w;
+  const PhiLayer& y = phi_layer(a, blockIdx.x, w);
+  const float *W1 = a.params + y.oW1, *b1 = W1 + a.hid * 4, *W2 = b1 + a.hid, *b2 = W2 + a.hid;
+  const int64_t npix = (int64_t)y.H * y.W;
+  const int64_t gp = (int64_t)w * 256 + threadIdx.x;
+  if (gp >= npix * a.nb) return;
+  const int smp = (int)(gp / npix), p = (int)(gp - smp * npix);
+  const int j = p / y.W, i = p - j * y.W;
+  const float* L = a.lv + smp * a.lv_stride + y.lv_off;
+  const float d0 = L[i], d1 = L[y.W + i], d2 = L[3 * y.W + j], d3 = L[3 * y.W + y.H + j];
+  float phi = b2[0];
+#pragma unroll
+  for (int k = 0; k < HC; ++k)
+    if (k < a.hid)
+      phi += W2[k] * tanh_nn(b1[k] + W1[k * 4] * d0 + W1[k * 4 + 1] * d1 + W1[k * 4 + 2] * d2 + W1[k * 4 + 3] * d3);
+  a.eta[y.eta_off + gp] = f2bf(exp_nn(-phi * phi));
+}
+
+// Gradients of Phi's parameters of all layers with one weight per node, from
+// dEta (se) of every node: through eta = exp(-Phi^2),
+//   dPhi = -2 Phi eta dEta,  dz_a = dPhi W2_a (1 - h_a^2),
+//   dW1[a][k] += dz_a d_k, db1[a] += dz_a, dW2[a] += dPhi h_a, db2 += dPhi.
+// Each thread sums its nodes (grid stride within the layer); the lanes of a wave
+// add up by a butterfly of register moves, the waves in order, into one partial
+// row per workgroup, [W1 (hid*4) | b1 (hid) | W2 (hid) | b2].
+//
+// Sum over a wavefront, lanes paired at distance 32, 16, 8, 4, 2, 1 (the row
+// rotations by 8 and 4 meet equal values there, so they pair as xor does).
+__device__ __forceinline__ float wave_sum_f32(float v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r.x) + __uint_as_float(r.y);
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r.x) + __uint_as_float(r.y);
+#define PPE_DPP_ADD(C) v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), C, 0xf, 0xf, true))
+  PPE_DPP_ADD(0x128);  // row_ror:8
+  PPE_DPP_ADD(0x124);  // row_ror:4
+  PPE_DPP_ADD(0x4E);   // quad_perm [2,3,0,1]
+  PPE_DPP_ADD(0xB1);   // quad_perm [1,0,3,2]
+#undef PPE_DPP_ADD
+  return v;
+}
+
+template <int HC>
+__global__ __launch_bounds__(256) void k_phi_grad(PhiArgs a) {
   constexpr int NV = HC * 6 + 1;  // accumulated values: W1 (4 HC), b1, W2, b2
   __shared__ float s_w[kWaves][NV];
+  int w;
+  const PhiLayer& y = phi_layer(a, blockIdx.x, w);
+  const float *W1 = a.params + y.oW1, *b1 = W1 + a.hid * 4, *W2 = b1 + a.hid, *b2 = W2 + a.hid;
+  const int64_t npix = (int64_t)y.H * y.W, ntot = npix * a.nb;
   float acc[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.f;
-  const int64_t npix = (int64_t)H * W, ntot = npix * nb;
-  for (int64_t gp = (int64_t)blockIdx.x * 256 + threadIdx.x; gp < ntot; gp += (int64_t)gridDim.x * 256) {
-    const int smp = (int)(gp / npix);
-    const int p = (int)(gp - smp * npix);
-    const int j = p / W, i = p - j * W;
-    const float* L = lv + smp * lv_stride;
-    const float d[4] = {L[i], L[W + i], L[3 * W + j], L[3 * W + H + j]};
-    // dEta and dX over the pixel's channels (eta: one value per pixel of each sample)
-    const float e = bf2f(eta[gp]);
-    const uint4* xr = (const uint4*)(x + gp * cin8);
-    uint4* gr = (uint4*)(dxb + gp * cin8);
-    float se = 0.f;
-    for (int c8 = 0; c8 < cin8 / 8; ++c8) {
-      const uint4 gv = gr[c8], xv = xr[c8];
-      const uint32_t ga[4] = {gv.x, gv.y, gv.z, gv.w}, xa[4] = {xv.x, xv.y, xv.z, xv.w};
-      uint32_t o[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float g0 = bf2f((bf16_t)(ga[k] & 0xffff)), g1 = bf2f((bf16_t)(ga[k] >> 16));
-        se += g0 * bf2f((bf16_t)(xa[k] & 0xffff)) + g1 * bf2f((bf16_t)(xa[k] >> 16));
-        o[k] = (uint32_t)f2bf(e * g0) | ((uint32_t)f2bf(e * g1) << 16);
-      }
-      gr[c8] = make_uint4(o[0], o[1], o[2], o[3]);
-    }
-    // Phi and its parameters' gradients at this node
+  for (int64_t gp = (int64_t)w * 256 + threadIdx.x; gp < ntot; gp += (int64_t)y.nwg * 256) {
+    const int smp = (int)(gp / npix), p = (int)(gp - smp * npix);
+    const int j = p / y.W, i = p - j * y.W;
+    const float* L = a.lv + smp * a.lv_stride + y.lv_off;
+    const float d[4] = {L[i], L[y.W + i], L[3 * y.W + j], L[3 * y.W + y.H + j]};
+    const float se = a.se[y.eta_off + gp];
     float h[HC];
     float phi = b2[0];
 #pragma unroll
-    for (int a = 0; a < HC; ++a) {
-      h[a] = 0.f;
-      if (a < hid) {
-        h[a] = tanh_nn(b1[a] + W1[a * 4] * d[0] + W1[a * 4 + 1] * d[1] + W1[a * 4 + 2] * d[2] + W1[a * 4 + 3] * d[3]);
-        phi += W2[a] * h[a];
+    for (int q = 0; q < HC; ++q) {
+      h[q] = 0.f;
+      if (q < a.hid) {
+        h[q] = tanh_nn(b1[q] + W1[q * 4] * d[0] + W1[q * 4 + 1] * d[1] + W1[q * 4 + 2] * d[2] + W1[q * 4 + 3] * d[3]);
+        phi += W2[q] * h[q];
       }
     }
     const float dphi = se * (-2.f * phi * exp_nn(-phi * phi));
 #pragma unroll
-    for (int a = 0; a < HC; ++a) {
-      if (a >= hid) continue;
-      const float dz = dphi * W2[a] * (1.f - h[a] * h[a]);
+    for (int q = 0; q < HC; ++q) {
+      if (q >= a.hid) continue;
+      const float dz = dphi * W2[q] * (1.f - h[q] * h[q]);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[a * 4 + k] += dz * d[k];
-      acc[HC * 4 + a] += dz;
-      acc[HC * 5 + a] += dphi * h[a];
+      for (int k = 0; k < 4; ++k) acc[q * 4 + k] += dz * d[k];
+      acc[HC * 4 + q] += dz;
+      acc[HC * 5 + q] += dphi * h[q];
     }
     acc[HC * 6] += dphi;
   }
-  // lanes of a wave (butterfly), then the waves in order
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    float v = acc[k];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    const float v = wave_sum_f32(acc[k]);
     if (lane == 0) s_w[wv][k] = v;
   }
   __syncthreads();
-  const int len = hid * 6 + 1;
-  float* row = part + (int64_t)blockIdx.x * len;
+  const int len = a.hid * 6 + 1;
+  float* row = a.part + (int64_t)blockIdx.x * len;
   for (int u = threadIdx.x; u < len; u += 256) {
-    // u: W1 (a * 4 + k) | b1 (a) | W2 (a) | b2
-    const int k = u < hid * 4 ? u : u < hid * 5 ? HC * 4 + (u - hid * 4) : u < hid * 6 ? HC * 5 + (u - hid * 5) : HC * 6;
+    // u: W1 (q * 4 + k) | b1 (q) | W2 (q) | b2
+    const int k = u < a.hid * 4 ? u : u < a.hid * 5 ? HC * 4 + (u - a.hid * 4) : u < a.hid * 6 ? HC * 5 + (u - a.hid * 5) : HC * 6;
     float t = 0.f;
-    for (int w = 0; w < kWaves; ++w) t += s_w[w][k];
+    for (int v = 0; v < kWaves; ++v) t += s_w[v][k];
     row[u] = t;
   }
 }
 
-int eta_bwd_node_len(int hid) { return hid * 6 + 1; }
+#define PPE_PHI_HC(K)                                  \
+  if (a.hid <= 8) K<8><<<wg, 256, 0, s>>>(a);          \
+  else if (a.hid <= 16) K<16><<<wg, 256, 0, s>>>(a);   \
+  else K<32><<<wg, 256, 0, s>>>(a)
 
-void launch_eta_bwd_node(int H, int W, int cin8, int hid, int nb, const float* lv, int64_t lv_stride,
-                         const float* W1, const float* b1, const float* W2, const float* b2, const bf16_t* x,
-                         const bf16_t* eta, bf16_t* dxb, float* part, int nparts, hipStream_t s) {
-  if (hid <= 8)
-    k_eta_bwd_node<8><<<nparts, 256, 0, s>>>(H, W, cin8, hid, nb, lv, lv_stride, W1, b1, W2, b2, x, eta, dxb, part);
-  else if (hid <= 16)
-    k_eta_bwd_node<16><<<nparts, 256, 0, s>>>(H, W, cin8, hid, nb, lv, lv_stride, W1, b1, W2, b2, x, eta, dxb, part);
-  else
-    k_eta_bwd_node<32><<<nparts, 256, 0, s>>>(H, W, cin8, hid, nb, lv, lv_stride, W1, b1, W2, b2, x, eta, dxb, part);
+void launch_eta_nodes(PhiArgs a, hipStream_t s) {
+  int wg = 0;
+  for (int k = 0; k < a.n; ++k) {
+    a.layer[k].wg0 = wg;
+    wg += (int)(((int64_t)a.layer[k].H * a.layer[k].W * a.nb + 255) / 256);
+  }
+  PPE_PHI_HC(k_eta_nodes);
 }
+
+// Workgroups per layer: one node per thread at least, kPhiParts at most.
+// Adds the layers' partial rows to the table of sums.
+void launch_phi_grad(PhiArgs a, float* grad, RowTable& t, hipStream_t s) {
+  const int len = a.hid * 6 + 1;
+  int wg = 0;
+  for (int k = 0; k < a.n; ++k) {
+    const int64_t n = (int64_t)a.layer[k].H * a.layer[k].W * a.nb;
+    a.layer[k].wg0 = wg;
+    a.layer[k].nwg = (int)std::min<int64_t>(kPhiParts, (n + 255) / 256);
+    t.row[t.n++] = RowSum{a.part + (int64_t)wg * len, a.layer[k].nwg, len, grad + a.layer[k].oW1};
+    wg += a.layer[k].nwg;
+  }
+  PPE_PHI_HC(k_phi_grad);
+}
+#undef PPE_PHI_HC
 
 void launch_sum_parts(const double* part, int n, double scale, double* out, hipStream_t s) {
   k_sum_parts<<<1, 64, 0, s>>>(part, n, scale, out);
