@@ -81,7 +81,7 @@ struct ConvGeo {
   int64_t x1_bstride;  // elements between samples of x1 (0 = shared by the batch)
   // optional coarse source: input channels [0, cu) come from xu, a buffer at
   // half the resolution (pixel (y, x) reads (y / 2, x / 2): the nearest
-  // upsampling of its values), pitch xu_pitch; cu a multiple of 32, cu <= c1
+  // upsampling of its values), pitch xu_pitch; cu <= c1
   const bf16_t* xu;
   int cu;
   int xu_pitch;

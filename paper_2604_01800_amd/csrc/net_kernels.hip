@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "conv_device.hpp"
 #include "net_common.hpp"
 #include "net_kernels.hpp"
 
@@ -34,56 +35,19 @@ namespace ppe {
 // past cout read as zero through a buffer resource that ends at the last
 // output channel. TAPS = 9 (3x3, zero padding) or 1 (1x1). UP = the output is
 // written to the 2x nearest-upsampled pixels of a finer level.
-constexpr int kCTH = 16, kCTW = 16;  // pixel tile of the convolution kernel
-
-template <int TN, int TAPS>
-struct ConvShape {
-  static constexpr int HALO = TAPS == 9 ? 1 : 0;
-  static constexpr int LW = kCTW + 2 * HALO, LH = kCTH + 2 * HALO;
-  static constexpr int NPIX = LW * LH;
-  // input channels staged per item: 32 for 3x3 layers, 64 for 1x1 layers (the
-  // packed weight layout is the same: a full 64-channel chunk of a 1x1 layer
-  // is two full 32-channel chunks)
-  static constexpr int CK = TAPS == 9 ? kConvCK : 2 * kConvCK;
-  static constexpr int G8 = CK / 8;                             // 8-channel groups of a staged pixel
-  static constexpr int PPR = 256 / G8;                          // pixels staged per round of 256 threads
-  static constexpr int CKP = CK + 8;                            // LDS pitch of a staged pixel (bf16)
-  static constexpr int SMAX = (TAPS * G8 + 3) / 4;              // K-steps of a full chunk
-  static constexpr int WQ = SMAX * 4;                           // 8-value groups of a full weight row
-  static constexpr int WKP = SMAX * 32 + 8;                     // LDS pitch of a staged weight row
-  static constexpr int NU = (NPIX + PPR - 1) / PPR;             // staged pixels per thread
-  static constexpr int NW = (TN * WQ + 255) / 256;              // weight groups per thread
-};
-
-// Registers of one item's loads, between issue and the write to LDS.
-template <int TN, int TAPS, int ETA>
-struct ConvStage {
-  static constexpr int NU = ConvShape<TN, TAPS>::NU;
-  uint4 x[NU], w[ConvShape<TN, TAPS>::NW];
-  uint4 e[ETA == kEtaChannel ? NU : 1];
-  uint32_t e1[ETA == kEtaNode ? NU : 1];
-};
 
 // This thread's staged pixels, fixed for the launch: pixel i sits at (ly, lx)
 // of the halo tile; xo[i] is its 8-channel group's byte offset from the halo
 // tile's first pixel in the input, eo[i] its byte offset in a per-node map
 // (both out of range for the slots past the halo tile).
-template <int TN, int TAPS>
+template <class S>
 struct ConvLane {
-  static constexpr int NU = ConvShape<TN, TAPS>::NU;
-  uint32_t xo[NU], eo[NU];
+  uint32_t xo[S::NU], eo[S::NU];
 };
 
-// Kept in registers for the launch where they fit (32 output channels per
-// workgroup); recomputed per item (about six VALU operations a pixel) where
-// the 64-channel kernel has no registers to spare.
-template <int TN>
-constexpr bool kKeepLane = TN == 32;
-
-template <int TN, int TAPS>
-__device__ __forceinline__ ConvLane<TN, TAPS> conv_lane(const ConvGeo& g) {
-  using S = ConvShape<TN, TAPS>;
-  ConvLane<TN, TAPS> ln;
+template <class S>
+__device__ __forceinline__ ConvLane<S> conv_lane(const ConvGeo& g) {
+  ConvLane<S> ln;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // not hoisted out of the item loop where recomputed
   const int c8 = tid % S::G8;
@@ -142,13 +106,11 @@ __device__ __forceinline__ void conv_commit_w(const uint4* w, int ck8, bf16_t* s
 // this thread's fixed one plus a scalar base; otherwise halo pixels outside
 // the image (and channel groups past the chunk or in the other source) get
 // an offset past the end, which reads as zero.
-template <int TN, int TAPS, int ETA, bool XU>
-__device__ __forceinline__ void conv_issue(ConvStage<TN, TAPS, ETA>& st, const ConvLane<TN, TAPS>& ln,
-                                           const ConvGeo& g, __amdgpu_buffer_rsrc_t xr, __amdgpu_buffer_rsrc_t x1r,
-                                           __amdgpu_buffer_rsrc_t xur, __amdgpu_buffer_rsrc_t er,
-                                           __amdgpu_buffer_rsrc_t wr, int Kp, int co0, int py0, int px0, int c0,
-                                           int ck8, int kbase, bool fast, bool fastu, bool wload) {
-  using S = ConvShape<TN, TAPS>;
+template <class S, int ETA, bool XU>
+__device__ __forceinline__ void conv_issue(ConvStage<S, ETA>& st, const ConvLane<S>& ln, const ConvGeo& g,
+                                           __amdgpu_buffer_rsrc_t xr, __amdgpu_buffer_rsrc_t x1r,
+                                           __amdgpu_buffer_rsrc_t xur, __amdgpu_buffer_rsrc_t er, int py0, int px0,
+                                           int c0, int ck8, bool fast, bool fastu) {
   if (XU && fastu) {
     // a full chunk of the coarse source on an interior tile: halo pixel
     // (ly, lx) reads coarse pixel (py0 / 2 - 1 + (ly + 1) / 2, px0 / 2 - 1 +
@@ -179,7 +141,7 @@ __device__ __forceinline__ void conv_issue(ConvStage<TN, TAPS, ETA>& st, const C
       }
     }
   } else if (fast) {
-    const ConvLane<TN, TAPS> lf = kKeepLane<TN> ? ln : conv_lane<TN, TAPS>(g);
+    const ConvLane<S> lf = S::KEEP ? ln : conv_lane<S>(g);
     const int pbase = (py0 - S::HALO) * g.W + (px0 - S::HALO);  // first halo pixel (>= 0 here)
     const int xb = (pbase * g.x_pitch + c0) * 2;
 #pragma unroll
@@ -236,14 +198,12 @@ __device__ __forceinline__ void conv_issue(ConvStage<TN, TAPS, ETA>& st, const C
       }
     }
   }
-  if (wload) conv_issue_w<TN, TAPS>(st.w, wr, Kp, co0, ck8, kbase);
 }
 
 // Writes one item's staged registers to LDS (inputs times eta).
-template <int TN, int TAPS, int ETA>
-__device__ __forceinline__ void conv_commit(const ConvStage<TN, TAPS, ETA>& st, int ck8, bool wload, bf16_t* s_x,
+template <class S, int ETA>
+__device__ __forceinline__ void conv_commit(const ConvStage<S, ETA>& st, int ck8, bool wload, bf16_t* s_x,
                                             bf16_t* s_w) {
-  using S = ConvShape<TN, TAPS>;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int c8 = tid % S::G8;
@@ -259,7 +219,7 @@ __device__ __forceinline__ void conv_commit(const ConvStage<TN, TAPS, ETA>& st, 
       }
     }
   }
-  if (wload) conv_commit_w<TN, TAPS>(st.w, ck8, s_w);
+  if (wload) conv_commit_w<S::TN, S::TAPS>(st.w, ck8, s_w);
 }
 
 // MFMA loop over the K-steps of one staged item. B fragments (staged
@@ -312,19 +272,8 @@ __device__ __forceinline__ void conv_mfma(f32x4_t (&acc)[TN / 16][4], const bf16
 // entries ordered by their first workgroup along x); a workgroup finds its
 // member, returns at once when the member's solve has decided, and then does
 // exactly the work of the same tile run in the member's own launch.
-// One 4-channel group of the DeepONet output contraction: BF16 activations
-// d (two packed pairs) times fold weights w, a product and three FMAs in
-// channel order. Both output paths (the separate kernel and the fused
-// convolution epilogue) use it, so they round alike.
-__device__ __forceinline__ float out_group4(uint2 d, float4 w) {
-  float e = __fmul_rn(bf2f((bf16_t)(d.x & 0xffff)), w.x);
-  e = __fmaf_rn(bf2f((bf16_t)(d.x >> 16)), w.y, e);
-  e = __fmaf_rn(bf2f((bf16_t)(d.y & 0xffff)), w.z, e);
-  return __fmaf_rn(bf2f((bf16_t)(d.y >> 16)), w.w, e);
-}
-
 template <int TN, int TAPS, bool UP, int ETA, bool WSTAT, bool GRP, bool XU, bool OUTF = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TN == 32 ? 3 : 2))) void k_conv(
     ConvGeo g, const bf16_t* __restrict__ x, const bf16_t* __restrict__ eta, const bf16_t* __restrict__ wp, int Kp,
     const float* __restrict__ bias, bf16_t* __restrict__ y, int tiles_per_wg, float* __restrict__ kpart, int ksplit,
     const ConvMember* __restrict__ mem, int nmem, OutFold of) {
@@ -333,6 +282,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ __attribute__((aligned(16))) bf16_t s_x[S::NPIX * S::CKP];
   __shared__ __attribute__((aligned(16))) bf16_t s_w[TN * S::WKP];
   __shared__ __attribute__((aligned(16))) float s_b[TN];
+  __shared__ __attribute__((aligned(16))) bf16_t s_t[4 * 512];  // stores' line buffers, one per wavefront
 
   int t0, smp, ksp, nbs;  // first tile, sample, K share, samples of the launch
   if constexpr (GRP) {
@@ -397,8 +347,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   const __amdgpu_buffer_rsrc_t pr = __builtin_amdgcn_make_buffer_rsrc(
       pool ? g.pool_y + smp * g.pool_bstride : y, (short)0,
       pool ? (int)((int64_t)(g.H / 2) * (g.W / 2) * g.pool_pitch * 2) : 0, 0x00020000);
-  ConvLane<TN, TAPS> ln;
-  if constexpr (kKeepLane<TN>) ln = conv_lane<TN, TAPS>(g);
+  ConvLane<S> ln;
+  if constexpr (S::KEEP) ln = conv_lane<S>(g);
   // input-channel chunks of this workgroup: all of them, or its share when
   // the K loop is split over ksplit workgroups
   const int nch_all = (g.cin8 + S::CK - 1) / S::CK;
@@ -423,7 +373,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
   constexpr bool wload = !WSTAT;
   // the loads of item it
-  auto issue = [&](ConvStage<TN, TAPS, ETA>& st, int it) {
+  auto issue = [&](ConvStage<S, ETA>& st, int it) {
     const int t = t0 + it / nch, c = c_lo + it - (it / nch) * nch;
     const int c0 = c * S::CK;
     const int ck8 = min(S::CK, g.cin8 - c0) / 8;
@@ -433,8 +383,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const bool fast = ck8 == S::G8 && (!XU || c0 >= g.cu) && c0 + S::CK <= g.c1 &&
                       (ETA != kEtaChannel || g.x_pitch == g.cin8) && interior;
     const bool fastu = XU && ck8 == S::G8 && c0 + S::CK <= g.cu && interior;
-    conv_issue<TN, TAPS, ETA, XU>(st, ln, g, xr, x1r, xur, er, wr, Kp, co0, py0, px0, c0, ck8, c * S::SMAX * 32, fast,
-                              fastu, wload);
+    conv_issue<S, ETA, XU>(st, ln, g, xr, x1r, xur, er, py0, px0, c0, ck8, fast, fastu);
+    if (wload) conv_issue_w<TN, TAPS>(st.w, wr, Kp, co0, ck8, c * S::SMAX * 32);
   };
   for (int it = 0; it < items; ++it) {
     const int t = t0 + it / nch, c = c_lo + it - (it / nch) * nch;
@@ -444,10 +394,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     // nothing of it is live from one item to the next). Issuing the next
     // item's loads before the current MFMA loop instead costs the 32-channel
     // kernel a resident workgroup per CU and was slower.
-    ConvStage<TN, TAPS, ETA> stg;
+    ConvStage<S, ETA> stg;
     issue(stg, it);
     __syncthreads();  // the previous item's MFMA loop is done with LDS
-    conv_commit<TN, TAPS, ETA>(stg, ck8, wload, s_x, s_w);
+    conv_commit<S, ETA>(stg, ck8, wload, s_x, s_w);
     __syncthreads();
 
     if (ck8 == S::G8)
@@ -456,135 +406,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       conv_mfma<TN, TAPS, 0>(acc, s_x, s_w, ck8, lane, wv);
     if (c + 1 < c_lo + nch) continue;
 
-    // Epilogue of tile t: lane holds out[co0 + mt*16 + 4*(lane>>4) + j][pixel (row NT*w+nt, col lane&15)].
-    if (ksplit > 1) {
-      // partial sums of this share of K, [ksplit][sample][pixel][gridDim.y * TN] FP32
-      const int cp = gridDim.y * TN;
-      float* pp = kpart + ((int64_t)ksp * nbs + smp) * g.H * g.W * cp;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int co = co0 + mt * 16 + 4 * (lane >> 4);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const int py = py0 + NT * wv + nt, px = px0 + (lane & 15);
-          if (co < g.cout && py < g.H && px < g.W)
-            *(f32x4_t*)(pp + ((int64_t)py * g.W + px) * cp + co) = acc[mt][nt];
-          acc[mt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        }
-      }
-      continue;
-    }
-    if constexpr (OUTF) {
-      // DeepONet output instead of the stored activations (TN = 32 and
-      // c0 <= 32: the workgroup holds every channel of its pixels). The
-      // lane's channel group q = 4 mt + (lane >> 4) takes the place of lane q
-      // of k_deeponet_out: the same BF16-rounded values, the same group sum,
-      // and the same pairwise order across groups (q ^ 4 within the lane, then
-      // lanes ^ 32 and ^ 16), so the result is that kernel's bit for bit.
-      static_assert(TN == 32 && !UP && !GRP, "fused output: 32 output channels per workgroup, plain launch");
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int py = py0 + NT * wv + nt, px = px0 + (lane & 15);
-        const bool pok = py < g.H && px < g.W;
-        const int64_t pix = (int64_t)py * g.W + px;
-        float sq[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const int col = mt * 16 + 4 * (lane >> 4);
-          const f32x4_t b = *(const f32x4_t*)(s_b + col);
-          float v[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = acc[mt][nt][j] + b[j];
-          if (g.act == 1) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = __builtin_amdgcn_fmed3f(v[j], 0.f, __builtin_inff());
-          } else if (g.act == 2) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = tanh_nn(v[j]);
-          }
-          const uint2 pk = {__builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){v[0], v[1]}, bf16x2_t)),
-                            __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){v[2], v[3]}, bf16x2_t))};
-          sq[mt] = 0.f;
-          if (pok && col < of.c0) sq[mt] += out_group4(pk, *(const float4*)(of.fold + pix * of.pitch + col));
-          acc[mt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        }
-        float sv = sq[0] + sq[1];
-        sv += __shfl_xor(sv, 32);
-        sv += __shfl_xor(sv, 16);
-        if (pok && lane < 16)
-          of.y[(int64_t)smp * g.H * g.W + pix] = of.gamma[0] * (sv + of.fold[pix * of.pitch + of.c0]);
-      }
-      continue;
-    }
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int col = mt * 16 + 4 * (lane >> 4);  // first of this lane's 4 channels within the workgroup's TN
-      const int co = co0 + col;
-      const bool cok = co < g.cout;
-      const f32x4_t b = *(const f32x4_t*)(s_b + col);
-      u32x2 pk[NT];  // the stored BF16 values (pooling reads them back)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int py = py0 + NT * wv + nt, px = px0 + (lane & 15);
-        float v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = acc[mt][nt][j] + b[j];
-        if (g.act == 1) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = __builtin_amdgcn_fmed3f(v[j], 0.f, __builtin_inff());
-        } else if (g.act == 2) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = tanh_nn(v[j]);
-        }
-        const u32x2 packed = {__builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){v[0], v[1]}, bf16x2_t)),
-                              __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){v[2], v[3]}, bf16x2_t))};
-        pk[nt] = packed;
-        if (!cok || py >= g.H || px >= g.W) continue;
-        if (!UP) {
-          const uint32_t o = (uint32_t)(((py * WO + px) * g.y_pitch + g.y_off + co) * 2);
-          __builtin_amdgcn_raw_buffer_store_b64(packed, yr, (int)o, 0, 0);
-        } else {
-#pragma unroll
-          for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int bb = 0; bb < 2; ++bb) {
-              const uint32_t o = (uint32_t)((((2 * py + a) * WO + 2 * px + bb) * g.y_pitch + g.y_off + co) * 2);
-              __builtin_amdgcn_raw_buffer_store_b64(packed, yr, (int)o, 0, 0);
-            }
-        }
-      }
-      if (!UP && pool) {
-        // 2 x 2 average into the next level: rows nt, nt + 1 of this lane and
-        // the same rows of the next column's lane; the sum in the order and
-        // rounding of the pooling kernel, from the stored BF16 values
-#pragma unroll
-        for (int nt = 0; nt < NT; nt += 2) {
-          const uint32_t w[4][2] = {{pk[nt].x, pk[nt].y},
-                                    {(uint32_t)__shfl_xor((int)pk[nt].x, 1), (uint32_t)__shfl_xor((int)pk[nt].y, 1)},
-                                    {pk[nt + 1].x, pk[nt + 1].y},
-                                    {(uint32_t)__shfl_xor((int)pk[nt + 1].x, 1),
-                                     (uint32_t)__shfl_xor((int)pk[nt + 1].y, 1)}};
-          float sm[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              sm[2 * h] += bf2f((bf16_t)(w[q][h] & 0xffff));
-              sm[2 * h + 1] += bf2f((bf16_t)(w[q][h] >> 16));
-            }
-          const int py = py0 + NT * wv + nt, px = px0 + (lane & 15);
-          if (cok && (lane & 1) == 0 && py < g.H && px < g.W) {
-            const u32x2 pooled = {(uint32_t)f2bf(0.25f * sm[0]) | ((uint32_t)f2bf(0.25f * sm[1]) << 16),
-                                  (uint32_t)f2bf(0.25f * sm[2]) | ((uint32_t)f2bf(0.25f * sm[3]) << 16)};
-            const uint32_t o = (uint32_t)((((py >> 1) * (g.W >> 1) + (px >> 1)) * g.pool_pitch + co) * 2);
-            __builtin_amdgcn_raw_buffer_store_b64(pooled, pr, (int)o, 0, 0);
-          }
-        }
-      }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
+    conv_epilogue<TN, NT, UP, OUTF>(acc, g, s_b, co0, py0 + NT * wv, px0 + (lane & 15), s_t + wv * 512, yr, pr, of, smp, nbs, ksp, ksplit,
+                                    kpart);
   }
 }
 
@@ -1149,15 +972,74 @@ int conv_default_tile(const ConvGeo& g, int nb) {
   return wgs64 >= 2 * (int64_t)conv_device_cus() ? 64 : 32;
 }
 
+// Tiles of the pipelined kernel.
+static int convp_tiles(const ConvGeo& g) { return ((g.W + kCTW - 1) / kCTW) * ((g.H + kCPH - 1) / kCPH); }
+
+// Whether a launch without a K split of `wgs` tiles runs pipelined, one workgroup per
+// compute unit: when the rounds of that many workgroups are at least
+// three quarters full. Smaller launches keep k_conv, whose smaller
+// workgroups share a compute unit (a 1024^2 forward takes 547 us with the line here,
+// 562 us with it at one half, 548 us at seven eighths; a mixed batch of 16 grids 3.40,
+// 3.42 and 3.41 ms).
+static bool convp_fills(int64_t wgs) {
+  const int64_t cus = conv_device_cus(), rounds = (wgs + cus - 1) / cus;
+  return 4 * wgs >= 3 * rounds * cus;
+}
+
+// Layers the pipelined kernel can run: chunks that one buffer holds (the coarse
+// source ends and the second source starts at a chunk; with 16, 24 or 40 channels at
+// the finest level some do not), offsets within a tile in 24-bit products.
+static bool convp_takes(const ConvGeo& g) {
+  return (!g.xu || g.cu % kConvCK == 0) && (!g.x1 || g.c1 % kConvCK == 0) && g.W <= (1 << 18) && 
+         std::max({g.x_pitch, g.x1_pitch, g.xu_pitch, g.cin8}) < (1 << 22);
+}
+
+// Output channels per workgroup of a pipelined launch: the tuned width, else 64
+// where that still fills the chip, else 32; 0: not pipelined.
+static int convp_tile(const ConvGeo& g, int nb, int tn) {
+  if (!convp_takes(g)) return 0;
+  const int64_t tiles = (int64_t)convp_tiles(g) * nb;
+  if ((tn ? tn == 64 : g.cout >= 64) && convp_fills(tiles * ((g.cout + 63) / 64))) return 64;
+  if (tn != 64 && convp_fills(tiles * ((g.cout + 31) / 32))) return 32;
+  return 0;
+}
+
+static void convp_go(int tn, const ConvGeo& g, int nb, int eta_mode, const bf16_t* x, const bf16_t* eta,
+                     const bf16_t* wp, int Kp, const float* bias, bf16_t* y, const OutFold* of, hipStream_t s) {
+  const int tiles = convp_tiles(g), cot = (g.cout + tn - 1) / tn;
+  const int64_t wgs = (int64_t)tiles * cot * nb, cus = conv_device_cus();
+  ConvpLaunch L;
+  L.run = (int)std::max<int64_t>(1, (wgs + cus - 1) / cus);
+  L.grid = dim3((tiles + L.run - 1) / L.run, cot, nb);
+  L.nch = (g.cin8 + kConvCK - 1) / kConvCK;
+  L.part = g.cin8 % kConvCK != 0;
+  L.eta_mode = eta_mode;
+  L.xu = g.xu != nullptr;
+  L.outf = of != nullptr;
+  L.g = g;
+  L.x = x;
+  L.eta = eta;
+  L.wp = wp;
+  L.Kp = Kp;
+  L.bias = bias;
+  L.y = y;
+  if (of) L.of = *of;
+  tn == 64 ? convp_launch64(L, s) : convp_launch32(L, s);
+}
+
 template <int TN, int TAPS, bool UP, int ETA>
 static void conv_go_eta(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t* eta, const bf16_t* wp, int Kp,
-                        const float* bias, bf16_t* y, hipStream_t s, float* kpart, int64_t kpart_elems) {
+                        const float* bias, bf16_t* y, hipStream_t s, float* kpart, int64_t kpart_elems, int tn) {
   const int tiles = conv_tiles(g);
   const int cot = (g.cout + TN - 1) / TN;
   const int cus = conv_device_cus();
   const int64_t wgs = (int64_t)tiles * cot * nb;
   const int nch = (g.cin8 + ConvShape<TN, TAPS>::CK - 1) / ConvShape<TN, TAPS>::CK;
   const int ks = conv_ksplit(g, nb, TN, nch, kpart != nullptr, kpart_elems, cot * TN);
+  if constexpr (TAPS == 9 && !UP) {
+    const int pt = ks == 1 ? convp_tile(g, nb, tn) : 0;
+    if (pt) return convp_go(pt, g, nb, ETA, x, eta, wp, Kp, bias, y, nullptr, s);
+  }
   // one chunk per workgroup: the weight slice is staged once
   const bool wstat = (nch + ks - 1) / ks == 1;
   // runs of tiles that fill the resident workgroups once
@@ -1202,25 +1084,33 @@ static void conv_group_plan_t(std::vector<ConvMember>& m, int64_t kpart_elems, C
   const ConvGeo& g0 = m[0].g;
   const int cot = (g0.cout + TN - 1) / TN;
   const int nch = (g0.cin8 + ConvShape<TN, TAPS>::CK - 1) / ConvShape<TN, TAPS>::CK;
-  int64_t wgs = 0, kwg = 0;
-  bool wstat = true;
+  int64_t wgs = 0, kwg = 0, pwgs = 0;
+  bool wstat = true, takes = TAPS == 9 && !UP;
   for (ConvMember& e : m) {
     // the K split of the member's own launch (its own tile width)
     e.ks = conv_ksplit(e.g, 1, e.tn ? e.tn : conv_default_tile(e.g, 1), nch, e.kpart != nullptr, kpart_elems,
                        cot * TN);
     wgs += (int64_t)conv_tiles(e.g) * cot * e.ks;
     wstat = wstat && (nch + e.ks - 1) / e.ks == 1;
+    takes = takes && convp_takes(e.g);
+    pwgs += (int64_t)convp_tiles(e.g) * cot * e.ks;
     e.kwg0 = (int)kwg;
     if (e.ks > 1) kwg += ((int64_t)e.g.H * e.g.W * (e.g.cout / 4) + 255) / 256;
   }
-  const int per_cu =
-      wstat ? conv_per_cu<TN, TAPS, UP, ETA, true, true>() : conv_per_cu<TN, TAPS, UP, ETA, false, true>();
+  // the members' tiles together fill the pipelined kernel's workgroups: its rule
+  L.pipe = takes && convp_fills(pwgs);
+  L.nch = nch;
+  L.part = g0.cin8 % kConvCK != 0;
+  if (L.pipe) wgs = pwgs;
+  const int per_cu = L.pipe ? 1
+                     : wstat ? conv_per_cu<TN, TAPS, UP, ETA, true, true>()
+                             : conv_per_cu<TN, TAPS, UP, ETA, false, true>();
   L.xu = m[0].g.xu != nullptr;
   const int64_t slots = (int64_t)conv_device_cus() * per_cu;
   const int run = (int)std::max<int64_t>(1, (wgs + slots - 1) / slots);
   int64_t wg = 0;
   for (ConvMember& e : m) {
-    e.nwt = (conv_tiles(e.g) + run - 1) / run;
+    e.nwt = ((L.pipe ? convp_tiles(e.g) : conv_tiles(e.g)) + run - 1) / run;
     e.wg0 = (int)wg;
     wg += (int64_t)e.nwt * e.ks;
   }
@@ -1241,7 +1131,22 @@ static void conv_group_launch_t(const ConvGroupLaunch& L, const ConvMember* dm, 
   const dim3 grid(L.gx, L.cot, 1);
   bool launched = false;
   if constexpr (TAPS == 9 && !UP) {
-    if (L.xu) {
+    if (L.pipe) {
+      ConvpLaunch P;
+      P.grid = grid;
+      P.nch = L.nch;
+      P.part = L.part;
+      P.eta_mode = ETA;
+      P.xu = L.xu != 0;
+      P.wp = wp;
+      P.Kp = Kp;
+      P.bias = bias;
+      P.run = L.run;
+      P.mem = dm;
+      P.nmem = L.nmem;
+      TN == 64 ? convp_launch64(P, s) : convp_launch32(P, s);
+      launched = true;
+    } else if (L.xu) {
       if (L.wstat)
         k_conv<TN, TAPS, UP, ETA, true, true, true><<<grid, 256, 0, s>>>(g0, nullptr, nullptr, wp, Kp, bias, nullptr,
                                                                          L.run, nullptr, 1, dm, L.nmem, OutFold{});
@@ -1319,9 +1224,12 @@ bool plan_conv_group(int taps, bool up, int Kp, std::vector<ConvMember>& m, int6
   // the group's tile width by the default rule over all members' workgroups
   bool wide = false;
   if (m[0].g.cout >= 64) {
-    int64_t wgs64 = 0;
-    for (const ConvMember& e : m) wgs64 += (int64_t)conv_tiles(e.g) * ((e.g.cout + 63) / 64);
-    wide = wgs64 >= 2 * (int64_t)conv_device_cus();
+    int64_t wgs64 = 0, pwgs64 = 0;
+    for (const ConvMember& e : m) {
+      wgs64 += (int64_t)conv_tiles(e.g) * ((e.g.cout + 63) / 64);
+      pwgs64 += (int64_t)convp_tiles(e.g) * ((e.g.cout + 63) / 64);
+    }
+    wide = wgs64 >= 2 * (int64_t)conv_device_cus() || (taps == 9 && !up && convp_fills(pwgs64));
   }
   return conv_group_dispatch(taps, up, L.eta, wide, [&](auto tn, auto tp, auto upc, auto et) {
     conv_group_plan_t<decltype(tn)::value, decltype(tp)::value, decltype(upc)::value, decltype(et)::value>(
@@ -1347,13 +1255,13 @@ void launch_conv_group(const ConvGroupLaunch& L, const ConvMember* d_mem, const 
 
 template <int TN, int TAPS, bool UP>
 static void conv_go(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t* eta, const bf16_t* wp, int Kp,
-                    const float* bias, bf16_t* y, hipStream_t s, float* kpart, int64_t kpart_elems) {
+                    const float* bias, bf16_t* y, hipStream_t s, float* kpart, int64_t kpart_elems, int tn) {
   if (!eta)
-    conv_go_eta<TN, TAPS, UP, kEtaNone>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
+    conv_go_eta<TN, TAPS, UP, kEtaNone>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
   else if (g.eta_node)
-    conv_go_eta<TN, TAPS, UP, kEtaNode>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
+    conv_go_eta<TN, TAPS, UP, kEtaNode>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
   else
-    conv_go_eta<TN, TAPS, UP, kEtaChannel>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
+    conv_go_eta<TN, TAPS, UP, kEtaChannel>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
 }
 
 template <int MT>
@@ -1376,6 +1284,8 @@ static void conv1x1_go(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t* 
 template <int ETA>
 static void conv_out_go(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t* eta, const bf16_t* wp, int Kp,
                         const float* bias, bf16_t* y, int nch, const OutFold& of, hipStream_t s) {
+  if (nch == 1 && convp_takes(g) && convp_fills((int64_t)convp_tiles(g) * nb))
+    return convp_go(32, g, nb, ETA, x, eta, wp, Kp, bias, y, &of, s);
   const int tiles = conv_tiles(g);
   const bool wstat = nch == 1;
   const int per_cu = wstat ? conv_per_cu<32, 9, false, ETA, true, false, false, true>()
@@ -1424,14 +1334,14 @@ void launch_conv(int taps, bool up, const ConvGeo& g, int nb, const bf16_t* x, c
   }
   const bool wide = (tn ? tn : conv_default_tile(g, nb)) == 64;
   if (taps == 9) {
-    if (wide) conv_go<64, 9, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
-    else conv_go<32, 9, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
+    if (wide) conv_go<64, 9, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
+    else conv_go<32, 9, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
   } else if (up) {
-    if (wide) conv_go<64, 1, true>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
-    else conv_go<32, 1, true>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
+    if (wide) conv_go<64, 1, true>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
+    else conv_go<32, 1, true>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
   } else {
-    if (wide) conv_go<64, 1, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
-    else conv_go<32, 1, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems);
+    if (wide) conv_go<64, 1, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
+    else conv_go<32, 1, false>(g, nb, x, eta, wp, Kp, bias, y, s, kpart, kpart_elems, tn);
   }
 }
 

@@ -15,6 +15,29 @@ struct TrunkDesc {
   int64_t oWh, obh;      // branch head (folded into the basis)
 };
 
+// A launch of the pipelined 3x3 convolution (conv_pipe.hpp): tiles of kCPH x 16
+// pixels, kCPT threads, runs of `run` tiles; mem: a grouped launch.
+constexpr int kCPH = 32;   // tile rows
+constexpr int kCPT = 512;  // threads
+struct ConvpLaunch {
+  dim3 grid;
+  int nch = 1;        // chunks of input channels
+  bool part = false;  // the last one holds fewer than four channel groups
+  int eta_mode = 0;   // kEta*
+  bool xu = false, outf = false;
+  ConvGeo g{};
+  const bf16_t *x = nullptr, *eta = nullptr, *wp = nullptr;
+  int Kp = 0;
+  const float* bias = nullptr;
+  bf16_t* y = nullptr;
+  int run = 1;
+  const ConvMember* mem = nullptr;
+  int nmem = 0;
+  OutFold of{};
+};
+void convp_launch32(const ConvpLaunch& L, hipStream_t s);
+void convp_launch64(const ConvpLaunch& L, hipStream_t s);
+
 // Floats of partial-sum room that lets every small layer split its K loop.
 int64_t conv_kpart_elems();
 // kpart (optional, kpart_elems floats): room for FP32 partial sums, which lets
@@ -45,6 +68,9 @@ struct ConvGroupLaunch {
   int taps = 9, up = 0, eta = 0, tn = 32, wstat = 0, run = 1, gx = 0, cot = 0, nmem = 0, split = 0, ksum_gx = 0;
   int skinny = 0;  // small 1x1 layers: the skinny GEMM with this many 16-channel tiles (2, 4, 8), else 0
   int xu = 0;      // the members have a coarse input source
+  bool pipe = false;   // the pipelined 3x3 kernel; nch, part: its chunks and whether the last is partial
+  int nch = 1;
+  bool part = false;
 };
 bool plan_conv_group(int taps, bool up, int Kp, std::vector<ConvMember>& m, int64_t kpart_elems,
                      ConvGroupLaunch& L);
