@@ -7,15 +7,17 @@
 
 namespace ppe {
 
-// Pipelined form of the 3x3 convolution for launches that fill the chip: the
+// Pipelined form of the 3x3 convolution for launches that fill the chip (TH = 32): the
 // same implicit GEMM with the same K order (so the same bits), in workgroups of
-// eight wavefronts over 32 x 16 pixel tiles, one workgroup per compute unit. What
+// eight wavefronts over 32 x 16 pixel tiles, one workgroup per compute unit; and for
+// those with at most one 16 x 16 tile per compute unit (TH = 16, four wavefronts, also
+// with a split K), which only ever wait for their own loads. What
 // bounded k_conv was the wait for an item's loads between two barriers, the vector
 // work beside the MFMAs (MFMA busy 12-28 %) and its stores of 8 bytes a lane. Here the
 // staged input is double buffered and one barrier separates items: a wavefront in turn
 // runs the MFMAs of an item, writes the next one to LDS, issues the loads of a later
 // one (two items in flight with 32 output channels and one chunk, layers that are bound
-// by memory) and stores its results; the second half of the wavefronts (the other one
+// by memory, and with 16-row tiles) and stores its results; the second half of the wavefronts (the other one
 // on each SIMD) does this half a turn later, so that one's vector work runs beside the
 // other's MFMAs. Weights stay in LDS for the launch where all chunks fit (WRES), else
 // their slices are double buffered too.
@@ -27,9 +29,9 @@ namespace ppe {
 // for 36 MT MFMAs. The 3x3 layers of a 1024^2 forward took 689 us with k_conv and take
 // 534 us; the largest (104 channels to 32 at 1024^2) 135 -> 88 us, 0.71 PFLOP/s.
 
-template <int TN>
+template <int TN, int TH>
 struct ConvP {
-  using S = ConvShape<TN, 9, kCPH, kCPT>;
+  using S = ConvShape<TN, 9, TH, TH * 16>;
   static constexpr int MT = TN / 16;
   static constexpr int XB = S::NPIX * 32;        // bf16 of one input buffer
   static constexpr int WB = S::SMAX * MT * 512;  // bf16 of one weight slice
@@ -47,26 +49,26 @@ struct ConvpLane {
   uint32_t wo;
 };
 
-template <int TN>
+template <int TN, int TH>
 __device__ __forceinline__ void convp_issue_w(uint4* w, uint32_t wo, __amdgpu_buffer_rsrc_t wr, int ck8,
                                               int kbase) {
-  using S = typename ConvP<TN>::S;
-  const int n = conv_chunk_steps(9, ck8 * 8) * ConvP<TN>::MT * 64;
+  using S = typename ConvP<TN, TH>::S;
+  const int n = conv_chunk_steps(9, ck8 * 8) * ConvP<TN, TH>::MT * 64;
 #pragma unroll
   for (int i = 0; i < S::NW; ++i) {
-    // threads per fragment column: kCPT / 64 fragments further on in the list of (step, tile)
-    const uint32_t off = (int)threadIdx.x + kCPT * i < n ? wo + i * (kCPT / 64 / ConvP<TN>::MT) * 64 : 0x80000000u;
+    // threads per fragment column: S::NTHR / 64 fragments further on in the list of (step, tile)
+    const uint32_t off = (int)threadIdx.x + S::NTHR * i < n ? wo + i * (S::NTHR / 64 / ConvP<TN, TH>::MT) * 64 : 0x80000000u;
     w[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wr, (int)off, kbase * 2, 0));
   }
 }
 
-template <int TN>
+template <int TN, int TH>
 __device__ __forceinline__ void convp_commit_w(const uint4* w, int ck8, bf16_t* s_w) {
-  using S = typename ConvP<TN>::S;
-  const int n = conv_chunk_steps(9, ck8 * 8) * ConvP<TN>::MT * 64;
+  using S = typename ConvP<TN, TH>::S;
+  const int n = conv_chunk_steps(9, ck8 * 8) * ConvP<TN, TH>::MT * 64;
 #pragma unroll
   for (int i = 0; i < S::NW; ++i) {
-    const int u = threadIdx.x + kCPT * i;
+    const int u = threadIdx.x + S::NTHR * i;
     if (u < n) *(uint4*)(s_w + u * 8) = w[i];
   }
 }
@@ -99,7 +101,7 @@ __device__ __forceinline__ void convp_issue_x(ConvStage<S, ETA>& st, const Convp
       const_cast<bf16_t*>(src + (half ? ub : pb) * pitch), (short)0, 0x7fffffff, 0x00020000);
   const __amdgpu_buffer_rsrc_t er = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t*>(eta + (ETA == kEtaNode ? pb : pb * g.cin8 + c0)), (short)0, 0x7fffffff, 0x00020000);
-  const bool whole = ck8 == 4 && py0 >= 1 && px0 >= 1 && py0 + kCPH + 1 <= g.H && px0 + kCTW + 1 <= g.W;
+  const bool whole = ck8 == 4 && py0 >= 1 && px0 >= 1 && py0 + S::TH + 1 <= g.H && px0 + kCTW + 1 <= g.W;
   const uint32_t pitch2 = pitch * 2, cb = c8 * 16;
   uint32_t bad[S::NU];
 #pragma unroll
@@ -155,10 +157,10 @@ __device__ __forceinline__ void convp_commit_x(const ConvStage<S, ETA>& st, int 
 // A full chunk: K-step = tap. swz[m]: this lane's element offset for a pixel
 // congruent to m (mod 8) past the lane's first halo pixel, less that pixel's
 // distance.
-template <int TN, bool AHEAD>
+template <int TN, int TH, bool AHEAD>
 __device__ __forceinline__ void convp_mfma_full(f32x4_t (&acc)[TN / 16][4], const bf16_t* s_x, const bf16_t* s_w,
                                                 const int (&swz)[8], int lane) {
-  constexpr int MT = TN / 16, LW = ConvP<TN>::S::LW;
+  constexpr int MT = TN / 16, LW = ConvP<TN, TH>::S::LW;
   bf16x8_t b[6][3];
   auto load_row = [&](int r) {
 #pragma unroll
@@ -196,10 +198,10 @@ __device__ __forceinline__ void convp_mfma_full(f32x4_t (&acc)[TN / 16][4], cons
 }
 
 // A chunk of ck8 < 4 channel groups: (tap, group) pairs in the packed order.
-template <int TN>
+template <int TN, int TH>
 __device__ __forceinline__ void convp_mfma_part(f32x4_t (&acc)[TN / 16][4], const bf16_t* s_x, const bf16_t* s_w,
                                                 int ck8, int lane, int wv) {
-  constexpr int MT = TN / 16, LW = ConvP<TN>::S::LW;
+  constexpr int MT = TN / 16, LW = ConvP<TN, TH>::S::LW;
   const int steps = conv_chunk_steps(9, ck8 * 8);
   const int p0 = 4 * wv * LW + (lane & 15);
   const int inv = ck8 == 3 ? 22 : 64 / ck8;  // G / ck8 = G * inv >> 6 for G < 28
@@ -223,30 +225,32 @@ __device__ __forceinline__ void convp_mfma_part(f32x4_t (&acc)[TN / 16][4], cons
 }
 
 // Place of an item in a workgroup's list: chunk (from the launch's first) and tile.
+template <int TH>
 struct ConvpPos {
   int k, py0, px0;
   __device__ __forceinline__ void next(int nch, int W) {
     if (++k < nch) return;
     k = 0;
     px0 += kCTW;
-    if (px0 >= W) px0 = 0, py0 += kCPH;
+    if (px0 >= W) px0 = 0, py0 += TH;
   }
 };
 
 // ONE: one chunk; PART: the last chunk holds fewer than four channel groups.
-template <int TN, int ETA, bool WRES, bool GRP, bool XU, bool OUTF, bool ONE, bool PART>
-__global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void k_convp(
+template <int TN, int TH, int ETA, bool WRES, bool GRP, bool XU, bool OUTF, bool ONE, bool PART>
+__global__ __launch_bounds__(TH * 16) __attribute__((amdgpu_waves_per_eu(TH == 16 && !ONE ? 1 : 2))) void k_convp(
     ConvGeo g, const bf16_t* __restrict__ x, const bf16_t* __restrict__ eta, const bf16_t* __restrict__ wp, int Kp,
-    const float* __restrict__ bias, bf16_t* __restrict__ y, int tiles_per_wg, const ConvMember* __restrict__ mem,
-    int nmem, OutFold of) {
-  using S = typename ConvP<TN>::S;
-  constexpr int MT = ConvP<TN>::MT, XB = ConvP<TN>::XB, WB = ConvP<TN>::WB;
+    const float* __restrict__ bias, bf16_t* __restrict__ y, int tiles_per_wg, float* __restrict__ kpart_l, int ksplit_l,
+    const ConvMember* __restrict__ mem, int nmem, OutFold of) {
+  using S = typename ConvP<TN, TH>::S;
+  constexpr int MT = ConvP<TN, TH>::MT, XB = ConvP<TN, TH>::XB, WB = ConvP<TN, TH>::WB;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // two input buffers, the stores' line buffers, the weight slices
   __shared__ __attribute__((aligned(16))) float s_b[TN];
-  bf16_t* s_w = smem + 2 * XB + kCPT / 64 * 512;
+  bf16_t* s_w = smem + 2 * XB + S::NTHR / 64 * 512;
 
-  float* kpart = nullptr;
-  int t0, smp, ksp, nbs, ksplit;
+  // K shares: a member's own, or the launch's (only the 16-row tiles are launched with a split)
+  float* kpart = TH == 16 ? kpart_l : nullptr;
+  int t0, smp, ksp, nbs, ksplit = TH == 16 ? ksplit_l : 1;
   if constexpr (GRP) {
     int lo = 0, hi = nmem - 1;  // the last member whose first workgroup is <= blockIdx.x
     while (lo < hi) {
@@ -272,13 +276,12 @@ __global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void 
     const int G = gridDim.x, per = (G + 7) / 8, b = blockIdx.x;
     const int xcd = b & 7, big = G - 8 * (per - 1);  // the first `big` XCDs hold per workgroups
     t0 = (xcd * per - max(0, xcd - big) + (b >> 3)) * tiles_per_wg;
-    smp = blockIdx.z;
-    ksp = 0;
-    ksplit = 1;
-    nbs = gridDim.z;
+    smp = blockIdx.z / ksplit;
+    ksp = blockIdx.z - smp * ksplit;
+    nbs = gridDim.z / ksplit;
   }
   const int tiles_x = (g.W + kCTW - 1) / kCTW;
-  const int tiles = tiles_x * ((g.H + kCPH - 1) / kCPH);
+  const int tiles = tiles_x * ((g.H + TH - 1) / TH);
   const int nt_wg = min(tiles_per_wg, tiles - t0);
   const int co0 = blockIdx.y * TN;
   x += smp * g.x_bstride;
@@ -326,16 +329,16 @@ __global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void 
     for (int m = 0; m < 8; ++m) swz[m] = p0 * 32 + (((lane >> 4) ^ (((p0 + m) >> 1) & 3)) * 8);
   }
   f32x4_t acc[MT][4];
-  constexpr int DEPTH = ONE && TN == 32 ? 2 : 1;  // items in flight to registers
+  constexpr int DEPTH = TN == 32 && (ONE || TH == 16) ? 2 : 1;  // items in flight to registers
   ConvStage<S, ETA> stg[DEPTH];
   float4 fpre[OUTF ? MT : 1][4];  // fold weights of the tile in acc
 
-  ConvpPos pc;  // the item computed
+  ConvpPos<TH> pc;  // the item computed
   pc.k = 0;
   pc.py0 = t0 / tiles_x;
   pc.px0 = (t0 - pc.py0 * tiles_x) * kCTW;
-  pc.py0 *= kCPH;
-  ConvpPos pl = pc;              // the next item to load
+  pc.py0 *= TH;
+  ConvpPos<TH> pl = pc;              // the next item to load
   int ni = 0, nc = 0, kc = 0;    // items loaded, items written to LDS, chunk of the next one to write
   auto issue = [&](ConvStage<S, ETA>& st) __attribute__((always_inline)) {
     if (ni >= items) return;
@@ -345,18 +348,18 @@ __global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void 
       convp_issue_x<S, ETA>(st, ln, g, x1 + c0 - g.c1, g.x1_pitch, false, eta, c0, pl.py0, pl.px0, ck8);
     else
       convp_issue_x<S, ETA>(st, ln, g, x + c0, g.x_pitch, false, eta, c0, pl.py0, pl.px0, ck8);
-    if constexpr (!WRES) convp_issue_w<TN>(st.w, ln.wo, wr, ck8, (c_lo + pl.k) * S::SMAX * 32);
+    if constexpr (!WRES) convp_issue_w<TN, TH>(st.w, ln.wo, wr, ck8, (c_lo + pl.k) * S::SMAX * 32);
     ++ni;
     pl.next(nch, g.W);
   };
   auto commit = [&](const ConvStage<S, ETA>& st) __attribute__((always_inline)) {
     if (nc >= items) return;
     convp_commit_x<S, ETA>(st, ck8_of(kc), smem + (nc & 1) * XB);
-    if constexpr (!WRES) convp_commit_w<TN>(st.w, ck8_of(kc), s_w + (nc & 1) * WB);
+    if constexpr (!WRES) convp_commit_w<TN, TH>(st.w, ck8_of(kc), s_w + (nc & 1) * WB);
     ++nc;
     kc = kc + 1 == nch ? 0 : kc + 1;
   };
-  auto mfma = [&](auto part, int it, const ConvpPos& p) __attribute__((always_inline)) {
+  auto mfma = [&](auto part, int it, const ConvpPos<TH>& p) __attribute__((always_inline)) {
     const bf16_t* sx = smem + (it & 1) * XB;
     const bf16_t* sw = s_w + (WRES ? p.k : it & 1) * WB;
     if (p.py0 + 4 * wv >= g.H) return;  // this wavefront's rows lie past the image
@@ -380,10 +383,11 @@ __global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void 
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) acc[m][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-    if constexpr (decltype(part)::value) convp_mfma_part<TN>(acc, sx, sw, ck8_of(p.k), lane, wv);
-    else convp_mfma_full<TN, WRES || TN == 32>(acc, sx, sw, swz, lane);
+    if (PART && (decltype(part)::value || (TH == 16 && !ONE && p.k == nfull)))
+      convp_mfma_part<TN, TH>(acc, sx, sw, ck8_of(p.k), lane, wv);
+    else if constexpr (!decltype(part)::value) convp_mfma_full<TN, TH, WRES || TN == 32>(acc, sx, sw, swz, lane);
   };
-  auto store = [&](const ConvpPos& p) __attribute__((always_inline)) {
+  auto store = [&](const ConvpPos<TH>& p) __attribute__((always_inline)) {
     const int pyr = p.py0 + 4 * wv;
     if (p.k + 1 < nch || pyr >= g.H) return;
     if constexpr (OUTF)
@@ -394,23 +398,23 @@ __global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void 
   };
   // The second half of the wavefronts stages one item further ahead, its barrier
   // between the MFMAs and the writes to LDS: item i + 2's buffer is item i's.
-  const bool late = wv >= kCPT / 128;
+  const bool late = wv >= S::NTHR / 128;
   // Loads of the first two items and of the resident weights are in flight together.
   {
     ConvStage<S, ETA> s1;
     issue(stg[0]);
     if constexpr (WRES) {
       uint4 w[2][S::NW];
-      convp_issue_w<TN>(w[0], ln.wo, wr, ck8_of(0), c_lo * S::SMAX * 32);
-      if (nch > 1) convp_issue_w<TN>(w[1], ln.wo, wr, ck8_of(1), (c_lo + 1) * S::SMAX * 32);
+      convp_issue_w<TN, TH>(w[0], ln.wo, wr, ck8_of(0), c_lo * S::SMAX * 32);
+      if (nch > 1) convp_issue_w<TN, TH>(w[1], ln.wo, wr, ck8_of(1), (c_lo + 1) * S::SMAX * 32);
       issue(s1);
-      convp_commit_w<TN>(w[0], ck8_of(0), s_w);
-      if (nch > 1) convp_commit_w<TN>(w[1], ck8_of(1), s_w + WB);
+      convp_commit_w<TN, TH>(w[0], ck8_of(0), s_w);
+      if (nch > 1) convp_commit_w<TN, TH>(w[1], ck8_of(1), s_w + WB);
       for (int k = 2; k < nch; k += 2) {
-        convp_issue_w<TN>(w[0], ln.wo, wr, ck8_of(k), (c_lo + k) * S::SMAX * 32);
-        if (k + 1 < nch) convp_issue_w<TN>(w[1], ln.wo, wr, ck8_of(k + 1), (c_lo + k + 1) * S::SMAX * 32);
-        convp_commit_w<TN>(w[0], ck8_of(k), s_w + k * WB);
-        if (k + 1 < nch) convp_commit_w<TN>(w[1], ck8_of(k + 1), s_w + (k + 1) * WB);
+        convp_issue_w<TN, TH>(w[0], ln.wo, wr, ck8_of(k), (c_lo + k) * S::SMAX * 32);
+        if (k + 1 < nch) convp_issue_w<TN, TH>(w[1], ln.wo, wr, ck8_of(k + 1), (c_lo + k + 1) * S::SMAX * 32);
+        convp_commit_w<TN, TH>(w[0], ck8_of(k), s_w + k * WB);
+        if (k + 1 < nch) convp_commit_w<TN, TH>(w[1], ck8_of(k + 1), s_w + (k + 1) * WB);
       }
     } else {
       issue(s1);
@@ -441,6 +445,11 @@ __global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void 
         if (it < items) step(last, stg[1]);
       }
     }
+  } else if constexpr (DEPTH == 2) {
+    while (it < items) {
+      step(std::false_type{}, stg[0]);
+      if (it < items) step(std::false_type{}, stg[1]);
+    }
   } else {
     for (int t = 0; t < nt_wg; ++t) {
       for (int k = 0; k < nfull; ++k) step(std::false_type{}, stg[0]);
@@ -450,31 +459,29 @@ __global__ __launch_bounds__(kCPT) __attribute__((amdgpu_waves_per_eu(2))) void 
 }
 
 // LDS of the pipelined kernel: two input buffers, the line buffers and nw weight slices.
-template <int TN>
+template <int TN, int TH>
 static size_t convp_lds(int nw) {
-  return (2 * (size_t)ConvP<TN>::XB + kCPT / 64 * 512 + (size_t)nw * ConvP<TN>::WB) * sizeof(bf16_t);
+  return (2 * (size_t)ConvP<TN, TH>::XB + TH * 16 / 64 * 512 + (size_t)nw * ConvP<TN, TH>::WB) * sizeof(bf16_t);
 }
 
 // Weight slices kept for the launch: all chunks where they fit beside the
 // input buffers (160 KB of LDS), else none (two slices in turn).
-template <int TN>
-static bool convp_wres(int nch) { return convp_lds<TN>(nch) <= 158 * 1024; }
+template <int TN, int TH>
+static bool convp_wres(int nch) { return convp_lds<TN, TH>(nch) <= 158 * 1024; }
 
 // The pipelined kernel of a launch: chunks resident or not, one chunk, a partial one.
-template <int TN, int ETA, bool GRP, bool XU, bool OUTF>
+template <int TN, int TH, int ETA, bool GRP, bool XU, bool OUTF>
 static void convp_launch_t(const ConvpLaunch& L, hipStream_t s) {
   auto go = [&](auto wres, auto one, auto pt) {
-    k_convp<TN, ETA, decltype(wres)::value, GRP, XU, OUTF, decltype(one)::value, decltype(pt)::value>
-        <<<L.grid, kCPT, convp_lds<TN>(wres ? L.nch : 2), s>>>(L.g, L.x, L.eta, L.wp, L.Kp, L.bias, L.y, L.run, L.mem,
-                                                               L.nmem, L.of);
+    k_convp<TN, TH, ETA, decltype(wres)::value, GRP, XU, OUTF, decltype(one)::value, decltype(pt)::value>
+        <<<L.grid, TH * 16, convp_lds<TN, TH>(wres ? L.nch : 2), s>>>(L.g, L.x, L.eta, L.wp, L.Kp, L.bias, L.y, L.run,
+                                                                      L.kpart, L.ks, L.mem, L.nmem, L.of);
   };
   const std::true_type yes;
   const std::false_type no;
   const bool part = L.part;
   if constexpr (OUTF) {  // (one chunk: the caller's rule)
     part ? go(yes, yes, yes) : go(yes, yes, no);
-  } else if constexpr (XU && TN == 64) {  // (at least 128 channels: the slices never all fit)
-    part ? go(no, no, yes) : go(no, no, no);
   } else {
     if constexpr (TN == 32 && !XU) {
       if (L.nch == 1) {
@@ -482,25 +489,39 @@ static void convp_launch_t(const ConvpLaunch& L, hipStream_t s) {
         return;
       }
     }
-    if (convp_wres<TN>(L.nch)) part ? go(yes, no, yes) : go(yes, no, no);
-    else part ? go(no, no, yes) : go(no, no, no);
+    // resident slices serve runs of tiles: not the 16-row tiles, of which a workgroup
+    // has one or two, nor 64 channels with a coarse source (at least 128 input channels)
+    if constexpr (TH == 32 && !(XU && TN == 64)) {
+      if (convp_wres<TN, TH>(L.nch)) {
+        part ? go(yes, no, yes) : go(yes, no, no);
+        return;
+      }
+    }
+    part ? go(no, no, yes) : go(no, no, no);
   }
 }
 
-template <int TN, int ETA>
+template <int TN, int TH, int ETA>
 static void convp_launch_eta(const ConvpLaunch& L, hipStream_t s) {
   if constexpr (TN == 32) {
-    if (L.outf) return convp_launch_t<TN, ETA, false, false, true>(L, s);
+    if (L.outf) return convp_launch_t<TN, TH, ETA, false, false, true>(L, s);
   }
-  if (L.mem) L.xu ? convp_launch_t<TN, ETA, true, true, false>(L, s) : convp_launch_t<TN, ETA, true, false, false>(L, s);
-  else L.xu ? convp_launch_t<TN, ETA, false, true, false>(L, s) : convp_launch_t<TN, ETA, false, false, false>(L, s);
+  if constexpr (TH == 32) {
+    if (L.mem) {
+      L.xu ? convp_launch_t<TN, TH, ETA, true, true, false>(L, s)
+           : convp_launch_t<TN, TH, ETA, true, false, false>(L, s);
+      return;
+    }
+  }
+  L.xu ? convp_launch_t<TN, TH, ETA, false, true, false>(L, s)
+       : convp_launch_t<TN, TH, ETA, false, false, false>(L, s);
 }
 
-template <int TN>
+template <int TN, int TH>
 static void convp_launch(const ConvpLaunch& L, hipStream_t s) {
-  if (L.eta_mode == kEtaNone) convp_launch_eta<TN, kEtaNone>(L, s);
-  else if (L.eta_mode == kEtaNode) convp_launch_eta<TN, kEtaNode>(L, s);
-  else convp_launch_eta<TN, kEtaChannel>(L, s);
+  if (L.eta_mode == kEtaNone) convp_launch_eta<TN, TH, kEtaNone>(L, s);
+  else if (L.eta_mode == kEtaNode) convp_launch_eta<TN, TH, kEtaNode>(L, s);
+  else convp_launch_eta<TN, TH, kEtaChannel>(L, s);
 }
 
 }  // namespace ppe

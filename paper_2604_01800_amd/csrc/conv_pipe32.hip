@@ -3,6 +3,6 @@
 
 namespace ppe {
 
-void convp_launch32(const ConvpLaunch& L, hipStream_t s) { convp_launch<32>(L, s); }
+void convp_launch32(const ConvpLaunch& L, hipStream_t s) { convp_launch<32, 32>(L, s); }
 
 }  // namespace ppe

@@ -3,6 +3,6 @@
 
 namespace ppe {
 
-void convp_launch64(const ConvpLaunch& L, hipStream_t s) { convp_launch<64>(L, s); }
+void convp_launch64(const ConvpLaunch& L, hipStream_t s) { convp_launch<64, 32>(L, s); }
 
 }  // namespace ppe

@@ -1004,13 +1004,16 @@ static int convp_tile(const ConvGeo& g, int nb, int tn) {
   return 0;
 }
 
-static void convp_go(int tn, const ConvGeo& g, int nb, int eta_mode, const bf16_t* x, const bf16_t* eta,
-                     const bf16_t* wp, int Kp, const float* bias, bf16_t* y, const OutFold* of, hipStream_t s) {
-  const int tiles = convp_tiles(g), cot = (g.cout + tn - 1) / tn;
-  const int64_t wgs = (int64_t)tiles * cot * nb, cus = conv_device_cus();
+static void convp_go(int tn, int th, const ConvGeo& g, int nb, int eta_mode, const bf16_t* x, const bf16_t* eta,
+                     const bf16_t* wp, int Kp, const float* bias, bf16_t* y, const OutFold* of, hipStream_t s,
+                     float* kpart = nullptr, int ks = 1) {
+  const int tiles = th == kCPH ? convp_tiles(g) : conv_tiles(g), cot = (g.cout + tn - 1) / tn;
+  const int64_t wgs = (int64_t)tiles * cot * nb * ks, cus = conv_device_cus();
   ConvpLaunch L;
+  L.kpart = kpart;
+  L.ks = ks;
   L.run = (int)std::max<int64_t>(1, (wgs + cus - 1) / cus);
-  L.grid = dim3((tiles + L.run - 1) / L.run, cot, nb);
+  L.grid = dim3((tiles + L.run - 1) / L.run, cot, nb * ks);
   L.nch = (g.cin8 + kConvCK - 1) / kConvCK;
   L.part = g.cin8 % kConvCK != 0;
   L.eta_mode = eta_mode;
@@ -1024,7 +1027,24 @@ static void convp_go(int tn, const ConvGeo& g, int nb, int eta_mode, const bf16_
   L.bias = bias;
   L.y = y;
   if (of) L.of = *of;
-  tn == 64 ? convp_launch64(L, s) : convp_launch32(L, s);
+  if (th != kCPH) convp_launch16(L, s);
+  else tn == 64 ? convp_launch64(L, s) : convp_launch32(L, s);
+}
+
+// Whether a launch that does not fill the larger tiles runs pipelined with 16-row
+// tiles: up to one workgroup per compute unit, where nothing else on the unit covers
+// k_conv's waits for loads (a 64^2 forward takes 154 us against 161 us with k_conv, a
+// hybrid multigrid solve at 512^2 15.0 against 15.7 ms). Above that k_conv has up to
+// three workgroups there.
+static bool convp_small(int64_t wgs) { return wgs <= (int64_t)conv_device_cus(); }
+
+// The sum over the K shares of a launch with a split.
+template <bool UP>
+static void conv_go_sum(const ConvGeo& g, int nb, int ks, int cp, const float* kpart, const float* bias, bf16_t* y,
+                        hipStream_t s) {
+  if (ks <= 1) return;
+  const int64_t n = (int64_t)g.H * g.W * (g.cout / 4);
+  k_conv_ksum<UP, false><<<dim3((unsigned)((n + 255) / 256), nb), 256, 0, s>>>(g, nb, ks, cp, kpart, bias, y, nullptr);
 }
 
 template <int TN, int TAPS, bool UP, int ETA>
@@ -1038,7 +1058,14 @@ static void conv_go_eta(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t*
   const int ks = conv_ksplit(g, nb, TN, nch, kpart != nullptr, kpart_elems, cot * TN);
   if constexpr (TAPS == 9 && !UP) {
     const int pt = ks == 1 ? convp_tile(g, nb, tn) : 0;
-    if (pt) return convp_go(pt, g, nb, ETA, x, eta, wp, Kp, bias, y, nullptr, s);
+    if (pt) return convp_go(pt, kCPH, g, nb, ETA, x, eta, wp, Kp, bias, y, nullptr, s);
+  }
+  bool small = false;
+  if constexpr (TAPS == 9 && !UP && TN == 32) small = convp_takes(g) && convp_small(wgs * ks);
+  if (small) {
+    convp_go(TN, kCTH, g, nb, ETA, x, eta, wp, Kp, bias, y, nullptr, s, kpart, ks);
+    conv_go_sum<UP>(g, nb, ks, cot * TN, kpart, bias, y, s);
+    return;
   }
   // one chunk per workgroup: the weight slice is staged once
   const bool wstat = (nch + ks - 1) / ks == 1;
@@ -1069,11 +1096,7 @@ static void conv_go_eta(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t*
       k_conv<TN, TAPS, UP, ETA, false, false, false><<<grid, 256, 0, s>>>(g, x, eta, wp, Kp, bias, y, run, kpart, ks,
                                                                           nullptr, 0, OutFold{});
   }
-  if (ks > 1) {
-    const int64_t n = (int64_t)g.H * g.W * (g.cout / 4);
-    k_conv_ksum<UP, false><<<dim3((unsigned)((n + 255) / 256), nb), 256, 0, s>>>(g, nb, ks, cot * TN, kpart, bias, y,
-                                                                                 nullptr);
-  }
+  conv_go_sum<UP>(g, nb, ks, cot * TN, kpart, bias, y, s);
 }
 
 // Grouped convolution: the members' K splits and runs of tiles, one launch
@@ -1285,7 +1308,9 @@ template <int ETA>
 static void conv_out_go(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t* eta, const bf16_t* wp, int Kp,
                         const float* bias, bf16_t* y, int nch, const OutFold& of, hipStream_t s) {
   if (nch == 1 && convp_takes(g) && convp_fills((int64_t)convp_tiles(g) * nb))
-    return convp_go(32, g, nb, ETA, x, eta, wp, Kp, bias, y, &of, s);
+    return convp_go(32, kCPH, g, nb, ETA, x, eta, wp, Kp, bias, y, &of, s);
+  if (nch == 1 && convp_takes(g) && convp_small((int64_t)conv_tiles(g) * nb))
+    return convp_go(32, kCTH, g, nb, ETA, x, eta, wp, Kp, bias, y, &of, s);
   const int tiles = conv_tiles(g);
   const bool wstat = nch == 1;
   const int per_cu = wstat ? conv_per_cu<32, 9, false, ETA, true, false, false, true>()

@@ -15,10 +15,9 @@ struct TrunkDesc {
   int64_t oWh, obh;      // branch head (folded into the basis)
 };
 
-// A launch of the pipelined 3x3 convolution (conv_pipe.hpp): tiles of kCPH x 16
-// pixels, kCPT threads, runs of `run` tiles; mem: a grouped launch.
-constexpr int kCPH = 32;   // tile rows
-constexpr int kCPT = 512;  // threads
+// A launch of the pipelined 3x3 convolution (conv_pipe.hpp): tiles of 32 or 16 rows of
+// 16 pixels, 16 threads a row, runs of `run` tiles, ks shares of K; mem: a grouped launch.
+constexpr int kCPH = 32;  // rows of the larger tile
 struct ConvpLaunch {
   dim3 grid;
   int nch = 1;        // chunks of input channels
@@ -31,12 +30,15 @@ struct ConvpLaunch {
   const float* bias = nullptr;
   bf16_t* y = nullptr;
   int run = 1;
+  float* kpart = nullptr;
+  int ks = 1;
   const ConvMember* mem = nullptr;
   int nmem = 0;
   OutFold of{};
 };
 void convp_launch32(const ConvpLaunch& L, hipStream_t s);
 void convp_launch64(const ConvpLaunch& L, hipStream_t s);
+void convp_launch16(const ConvpLaunch& L, hipStream_t s);  // 32 channels, 16-row tiles
 
 // Floats of partial-sum room that lets every small layer split its K loop.
 int64_t conv_kpart_elems();

@@ -56,7 +56,8 @@ def test_batch_of_tiles_matches_oracle(ppe, nx, ny, L, C, eta, sp, nb):
 @pytest.mark.parametrize("C,eta", [(32, 2), (24, 1), (32, 0)])
 def test_grouped_equals_single(ppe, C, eta):
     """Forwards of grids of several sizes in grouped launches: each grid's result is that
-    of its own forward, bit for bit (the K split is the grid's own)."""
+    of its own forward, bit for bit (the K split is the grid's own; alone, the small
+    grids run tiles of 16 rows)."""
     cfg = onet.NetConfig(levels=3, base_channels=C, use_eta=eta, use_spacing=1)
     net, _ = make_net(ppe, cfg, seed=11 + C)
     sizes = [(64, 48), (200, 136), (96, 320), (512, 264), (256, 256), (128, 128), (512, 264)]
