@@ -13,8 +13,6 @@ struct PcgArgs {
   float *xc, *r, *p0, *p1;  // [nb][N] each
   float* r1;                // [nb][N] second residual buffer (single-reduction iteration)
   double *partA, *partB;    // [nb][P], [nb][2][P]
-  const double* rzp;        // shares of r.z of a supplied z (Prz per solve, rz_stride apart): the
-  int Prz, rz_stride;       // second row of partB, or the V-cycle's own array
   double* part1;            // [2][nb][5][P] sums of the single-reduction iteration
   int P2;                   // workgroups per solve of the two-iteration form (56-column tiles)
   double* part2;            // [2][nb][11][P2] sums of the two-iteration form
@@ -38,6 +36,10 @@ struct PcgArgs {
   // Residual history (device [nb][hist_cap] FP64, NULL when not recorded).
   double* hist;
   int hist_cap;
+  // Shares of r.z of a supplied z (Prz per solve, rz_stride apart): the second
+  // row of partB, or the V-cycle's own array.
+  int Prz, rz_stride;
+  const double* rzp;
 };
 
 dim3 stencil_grid(const Coef& c, int R, int nb);
