@@ -397,11 +397,13 @@ __global__ __launch_bounds__(TH * 16) __attribute__((amdgpu_waves_per_eu(TH == 1
                                                 ksplit, kpart);
   };
   // The second half of the wavefronts stages one item further ahead, its barrier
-  // between the MFMAs and the writes to LDS: item i + 2's buffer is item i's. Not with
-  // 16-row tiles, whose four wavefronts have a SIMD each: the second item's wait would
-  // only come before the first barrier (a 64^2 forward takes 154.5 us with it, 145.4
-  // without).
-  const bool late = TH == 32 && wv >= S::NTHR / 128;
+  // between the MFMAs and the writes to LDS: item i + 2's buffer is item i's. (A 1024^2
+  // forward takes 568 us without this, 16 mixed grids 3.50 instead of 3.40 ms.) Not with
+  // 16-row tiles, whose four wavefronts have a SIMD each, nor with up to four items: there
+  // the wait for the second item before the first barrier costs more (a 64^2 forward
+  // takes 154.5 us with it and 145.4 without; 1024^2 555.3 and 552.9 with the line at
+  // four, 559 at eight).
+  const bool late = TH == 32 && (GRP || items > 4) && wv >= S::NTHR / 128;
   // Loads of the first two items and of the resident weights are in flight together.
   {
     ConvStage<S, ETA> s1;
