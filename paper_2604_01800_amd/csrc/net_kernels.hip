@@ -1033,8 +1033,8 @@ static void convp_go(int tn, int th, const ConvGeo& g, int nb, int eta_mode, con
 
 // Whether a launch that does not fill the larger tiles runs pipelined with 16-row
 // tiles: up to one workgroup per compute unit, where nothing else on the unit covers
-// k_conv's waits for loads (a 64^2 forward takes 154 us against 161 us with k_conv, a
-// hybrid multigrid solve at 512^2 15.0 against 15.7 ms). Above that k_conv has up to
+// k_conv's waits for loads (a 64^2 forward takes 146 us against 161 us with k_conv, a
+// hybrid multigrid solve at 512^2 14.6 against 15.7 ms). Above that k_conv has up to
 // three workgroups there.
 static bool convp_small(int64_t wgs) { return wgs <= (int64_t)conv_device_cus(); }
 
