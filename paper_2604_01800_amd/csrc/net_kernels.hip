@@ -7,6 +7,7 @@
 
 #include "common.hpp"
 #include "conv_device.hpp"
+#include "launch_plan.hpp"
 #include "net_common.hpp"
 #include "net_kernels.hpp"
 
@@ -975,15 +976,22 @@ int conv_default_tile(const ConvGeo& g, int nb) {
 // Tiles of the pipelined kernel.
 static int convp_tiles(const ConvGeo& g) { return ((g.W + kCTW - 1) / kCTW) * ((g.H + kCPH - 1) / kCPH); }
 
-// Whether a launch without a K split of `wgs` tiles runs pipelined, one workgroup per
-// compute unit: when the rounds of that many workgroups are at least
-// three quarters full. Smaller launches keep k_conv, whose smaller
-// workgroups share a compute unit (a 1024^2 forward takes 547 us with the line here,
-// 562 us with it at one half, 548 us at seven eighths; a mixed batch of 16 grids 3.40,
-// 3.42 and 3.41 ms).
-static bool convp_fills(int64_t wgs) {
-  const int64_t cus = conv_device_cus(), rounds = (wgs + cus - 1) / cus;
-  return 4 * wgs >= 3 * rounds * cus;
+static ConvpPart convp_part(const ConvGeo& g, int64_t copies) {
+  static_assert(kCPH == 2 * kCTH, "two of k_conv's tiles to one");
+  return {convp_tiles(g), copies, conv_tiles(g)};
+}
+
+// Whether a launch without a K split of `copies` times these tiles runs pipelined, one
+// workgroup per compute unit: when the tiles alone fill three quarters of their rounds
+// (a 1024^2 forward takes 547 us with the line here, 562 us with it at one half, 548 us at
+// seven eighths), and, cut into runs that end with their images, two thirds (6 grids of 256 x 256 take
+// 318 us with the line here, 325 at three quarters, 321 at one half); where they take more than
+// a tile each, the halves of the tiles that hold rows have to be half of that as well (150 grids
+// of 64 x 64, whose third level has 16 rows, take 632 us with this and 688 without; one round
+// of single tiles, as 64 such grids are, takes 273 us pipelined and 285 not). Smaller launches keep
+// k_conv, whose smaller workgroups share a compute unit.
+static bool convp_fills(const ConvGeo& g, int64_t copies) {
+  return convp_runs({convp_part(g, copies)}, conv_device_cus()).fills;
 }
 
 // Layers the pipelined kernel can run: chunks that one buffer holds (the coarse
@@ -998,9 +1006,8 @@ static bool convp_takes(const ConvGeo& g) {
 // where that still fills the chip, else 32; 0: not pipelined.
 static int convp_tile(const ConvGeo& g, int nb, int tn) {
   if (!convp_takes(g)) return 0;
-  const int64_t tiles = (int64_t)convp_tiles(g) * nb;
-  if ((tn ? tn == 64 : g.cout >= 64) && convp_fills(tiles * ((g.cout + 63) / 64))) return 64;
-  if (tn != 64 && convp_fills(tiles * ((g.cout + 31) / 32))) return 32;
+  if ((tn ? tn == 64 : g.cout >= 64) && convp_fills(g, (int64_t)nb * ((g.cout + 63) / 64))) return 64;
+  if (tn != 64 && convp_fills(g, (int64_t)nb * ((g.cout + 31) / 32))) return 32;
   return 0;
 }
 
@@ -1008,11 +1015,10 @@ static void convp_go(int tn, int th, const ConvGeo& g, int nb, int eta_mode, con
                      const bf16_t* wp, int Kp, const float* bias, bf16_t* y, const OutFold* of, hipStream_t s,
                      float* kpart = nullptr, int ks = 1) {
   const int tiles = th == kCPH ? convp_tiles(g) : conv_tiles(g), cot = (g.cout + tn - 1) / tn;
-  const int64_t wgs = (int64_t)tiles * cot * nb * ks, cus = conv_device_cus();
   ConvpLaunch L;
   L.kpart = kpart;
   L.ks = ks;
-  L.run = (int)std::max<int64_t>(1, (wgs + cus - 1) / cus);
+  L.run = (int)convp_runs({{tiles, (int64_t)cot * nb * ks, 2 * tiles}}, conv_device_cus()).run;
   L.grid = dim3((tiles + L.run - 1) / L.run, cot, nb * ks);
   L.nch = (g.cin8 + kConvCK - 1) / kConvCK;
   L.part = g.cin8 % kConvCK != 0;
@@ -1107,7 +1113,8 @@ static void conv_group_plan_t(std::vector<ConvMember>& m, int64_t kpart_elems, C
   const ConvGeo& g0 = m[0].g;
   const int cot = (g0.cout + TN - 1) / TN;
   const int nch = (g0.cin8 + ConvShape<TN, TAPS>::CK - 1) / ConvShape<TN, TAPS>::CK;
-  int64_t wgs = 0, kwg = 0, pwgs = 0;
+  int64_t wgs = 0, kwg = 0;
+  std::vector<ConvpPart> parts;
   bool wstat = true, takes = TAPS == 9 && !UP;
   for (ConvMember& e : m) {
     // the K split of the member's own launch (its own tile width)
@@ -1116,21 +1123,20 @@ static void conv_group_plan_t(std::vector<ConvMember>& m, int64_t kpart_elems, C
     wgs += (int64_t)conv_tiles(e.g) * cot * e.ks;
     wstat = wstat && (nch + e.ks - 1) / e.ks == 1;
     takes = takes && convp_takes(e.g);
-    pwgs += (int64_t)convp_tiles(e.g) * cot * e.ks;
+    parts.push_back(convp_part(e.g, (int64_t)cot * e.ks));
     e.kwg0 = (int)kwg;
     if (e.ks > 1) kwg += ((int64_t)e.g.H * e.g.W * (e.g.cout / 4) + 255) / 256;
   }
   // the members' tiles together fill the pipelined kernel's workgroups: its rule
-  L.pipe = takes && convp_fills(pwgs);
+  const ConvpRuns runs = takes ? convp_runs(parts, conv_device_cus()) : ConvpRuns{};
+  L.pipe = runs.fills;
   L.nch = nch;
   L.part = g0.cin8 % kConvCK != 0;
-  if (L.pipe) wgs = pwgs;
-  const int per_cu = L.pipe ? 1
-                     : wstat ? conv_per_cu<TN, TAPS, UP, ETA, true, true>()
-                             : conv_per_cu<TN, TAPS, UP, ETA, false, true>();
+  const int per_cu =
+      wstat ? conv_per_cu<TN, TAPS, UP, ETA, true, true>() : conv_per_cu<TN, TAPS, UP, ETA, false, true>();
   L.xu = m[0].g.xu != nullptr;
   const int64_t slots = (int64_t)conv_device_cus() * per_cu;
-  const int run = (int)std::max<int64_t>(1, (wgs + slots - 1) / slots);
+  const int run = L.pipe ? (int)runs.run : (int)std::max<int64_t>(1, (wgs + slots - 1) / slots);
   int64_t wg = 0;
   for (ConvMember& e : m) {
     e.nwt = ((L.pipe ? convp_tiles(e.g) : conv_tiles(e.g)) + run - 1) / run;
@@ -1247,12 +1253,13 @@ bool plan_conv_group(int taps, bool up, int Kp, std::vector<ConvMember>& m, int6
   // the group's tile width by the default rule over all members' workgroups
   bool wide = false;
   if (m[0].g.cout >= 64) {
-    int64_t wgs64 = 0, pwgs64 = 0;
+    int64_t wgs64 = 0;
+    std::vector<ConvpPart> parts64;
     for (const ConvMember& e : m) {
       wgs64 += (int64_t)conv_tiles(e.g) * ((e.g.cout + 63) / 64);
-      pwgs64 += (int64_t)convp_tiles(e.g) * ((e.g.cout + 63) / 64);
+      parts64.push_back(convp_part(e.g, (e.g.cout + 63) / 64));
     }
-    wide = wgs64 >= 2 * (int64_t)conv_device_cus() || (taps == 9 && !up && convp_fills(pwgs64));
+    wide = wgs64 >= 2 * (int64_t)conv_device_cus() || (taps == 9 && !up && convp_runs(parts64, conv_device_cus()).fills);
   }
   return conv_group_dispatch(taps, up, L.eta, wide, [&](auto tn, auto tp, auto upc, auto et) {
     conv_group_plan_t<decltype(tn)::value, decltype(tp)::value, decltype(upc)::value, decltype(et)::value>(
@@ -1307,7 +1314,7 @@ static void conv1x1_go(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t* 
 template <int ETA>
 static void conv_out_go(const ConvGeo& g, int nb, const bf16_t* x, const bf16_t* eta, const bf16_t* wp, int Kp,
                         const float* bias, bf16_t* y, int nch, const OutFold& of, hipStream_t s) {
-  if (nch == 1 && convp_takes(g) && convp_fills((int64_t)convp_tiles(g) * nb))
+  if (nch == 1 && convp_takes(g) && convp_fills(g, nb))
     return convp_go(32, kCPH, g, nb, ETA, x, eta, wp, Kp, bias, y, &of, s);
   if (nch == 1 && convp_takes(g) && convp_small((int64_t)conv_tiles(g) * nb))
     return convp_go(32, kCTH, g, nb, ETA, x, eta, wp, Kp, bias, y, &of, s);
