@@ -162,7 +162,7 @@ bool height_ok(int form, int R) {
 }
 
 // Number of compute units of the current device (256 on MI355X).
-static int device_cus() {
+int device_cus() {
   static int cus = 0;
   if (cus == 0) {
     int dev = 0, n = 0;

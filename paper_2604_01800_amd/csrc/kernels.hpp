@@ -42,6 +42,7 @@ struct PcgArgs {
   const double* rzp;
 };
 
+int device_cus();  // compute units of the current device
 dim3 stencil_grid(const Coef& c, int R, int nb);
 dim3 stencil_grid2(const Coef& c, int R, int nb);
 void launch_apply_f32(const Coef& c, int nb, const float* x, float* y, int R, hipStream_t s);

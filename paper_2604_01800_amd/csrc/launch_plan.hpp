@@ -96,4 +96,17 @@ inline ConvpRuns convp_runs(const std::vector<ConvpPart>& parts, int64_t cus) {
   return best;
 }
 
+// Whether the coarsest multigrid solve (nx x ny cells, nb right-hand sides) takes the two
+// launches that load every matrix value ahead. Their first one runs a workgroup per mode and
+// right-hand side, one on a compute unit (registers), and a round of them takes as
+// long for short axes as for axes of 128 cells, whereas the three launches get
+// shorter with the axes. Coarsest solve, two launches against three: 17 and 26 us at 128 x 128 x 2,
+// 28 and 32 us at 128 x 128 x 4 (two rounds), 47 and 47 us at 128 x 128 x 8; 24 and 22 us at 80 x 64 x 4,
+// 26 and 17 us at 64 x 32 x 8, 36 and 21 us at 96 x 32 x 8. A V-cycle of 64 right-hand sides on 256 x 256 takes
+// 162 us with two launches and 96 us with three, of 128 on 128 x 128 153 and 99 us.
+inline bool mg_two_launches(int64_t nx, int64_t ny, int64_t nb, int64_t cus) {
+  const int64_t rounds = (nx * nb + cus - 1) / cus;
+  return rounds == 1 || std::min(nx, ny) > std::min<int64_t>(32 * rounds, 96);
+}
+
 }  // namespace ppe

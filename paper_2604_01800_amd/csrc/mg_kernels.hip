@@ -34,6 +34,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "launch_plan.hpp"
 #include "mg_internal.hpp"
 #include "stencil.hpp"
 
@@ -376,7 +377,8 @@ __global__ __launch_bounds__(kBlock) void k_mg_cbwd(CoarseArgs a) {
 }
 
 // The coarsest solve for axes of at most kMgSmall cells (a 1024 x 1024 grid at
-// four levels has 128 x 128): two launches in place of the three above. What
+// four levels has 128 x 128) and few right-hand sides (mg_two_launches): two launches in
+// place of the three above. What
 // bounds it is the latency of its chain of dense transforms, so every matrix
 // value is loaded before the first product needs one: thread (j, part) keeps the
 // rows [32 part, 32 part + 32) of each transform's column j in registers, the
@@ -385,6 +387,11 @@ __global__ __launch_bounds__(kBlock) void k_mg_cbwd(CoarseArgs a) {
 // with half of their threads idle: 19.1 us at 128 x 128, against 8.1 + 6.0 us here.
 // (On FP64 matrix cores, 16 modes per workgroup, the same work took 39 us: eight
 // compute units then load all of the matrices.)
+//
+// The line at 128 cells is this layout's: four parts of 32 rows of two FP64 matrices are 128
+// registers of each of 512 threads. An axis of 129 to 256 cells would take twice the rows (more
+// registers than a thread of such a workgroup has) or twice the threads (the most a workgroup has, at half
+// the registers each), so it keeps the three launches.
 constexpr int kMgSmall = 128;
 constexpr int kMgParts = 4;
 constexpr int kMgPer = kMgSmall / kMgParts;  // matrix rows per thread
@@ -488,7 +495,8 @@ void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {
   const int L = m.L;
   const Cheb k = cheb_consts();
   // the two-launch coarsest solve reads a transposed right-hand side
-  const bool small = L > 1 && m.nxc <= kMgSmall && m.nyc <= kMgSmall;
+  const bool small =
+      L > 1 && m.nxc <= kMgSmall && m.nyc <= kMgSmall && mg_two_launches(m.nxc, m.nyc, nb, device_cus());
   auto rows = [&](int l) { return mg_rows((int64_t)m.lv[l].nx * m.lv[l].ny * nb); };
   // level l's arguments; the fine level reads the PCG residual and writes z
   auto level = [&](int l) {

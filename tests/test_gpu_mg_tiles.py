@@ -36,3 +36,22 @@ def test_vcycle_at_tile_edges(nx, ny, levels, nb):
         want = H.apply(r[k].astype(np.float64))
         got = z[k].cpu().numpy().astype(np.float64)
         assert np.linalg.norm(got - want) <= 2e-5 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("nx,ny,levels,nb", [
+    (64, 64, 4, 32), (64, 64, 4, 33),    # 256 and 264 workgroups of the first coarse launch: two and three launches
+    (256, 140, 2, 4), (256, 128, 2, 3),  # two rounds of them, with 70 and with 64 rows: two and three launches
+])
+def test_vcycle_of_many_right_hand_sides(nx, ny, levels, nb):
+    from paper_2604_01800_amd import ppe
+    rng = np.random.default_rng(nx + 7 * ny + nb)
+    g = inputs.random_stretched_grid(nx, ny, rng)
+    H = omg.Hierarchy(g, levels=levels)
+    r = rng.standard_normal((nb, ny, nx))
+    r = (r - r.mean(axis=(1, 2), keepdims=True)).astype(np.float32)
+    z = torch.zeros((nb, ny, nx), dtype=torch.float32, device="cuda")
+    ppe.ppe_apply_precond(ppe.ppe_problem_create(g), torch.from_numpy(r).cuda(), z,
+                          ppe.ppe_solve_opts_default(precond=ppe.PPE_PC_MG, mg_levels=levels))
+    for k in (0, nb // 2, nb - 1):
+        want = H.apply(r[k].astype(np.float64))
+        assert np.linalg.norm(z[k].cpu().numpy() - want) <= 2e-5 * np.linalg.norm(want)

@@ -15,6 +15,12 @@ MAIN = r"""
 int main() {
   long long cus, n;
   while (std::scanf("%lld %lld", &cus, &n) == 2) {
+    if (n == 0) {
+      long long nx, ny, nb;
+      if (std::scanf("%lld %lld %lld", &nx, &ny, &nb) != 3) return 1;
+      std::printf("%d\n", (int)ppe::mg_two_launches(nx, ny, nb, cus));
+      continue;
+    }
     std::vector<ppe::ConvpPart> parts(n);
     for (auto& p : parts) {
       long long t, c, h;
@@ -100,3 +106,14 @@ def test_batches_take_one_round_of_workgroups(exe, nx, ny, images):
 def test_half_empty_tiles(exe, nx, ny, images, want):
     (_, _, _, fills), = run_plans(exe, [(256, [image(nx, ny, images)])])
     assert fills == want
+
+
+@pytest.mark.parametrize("nx,ny,nb,want", [
+    (128, 128, 1, 1), (8, 8, 32, 1), (32, 128, 8, 1),      # one round of the first launch
+    (8, 8, 64, 0), (16, 16, 128, 0), (32, 32, 64, 0), (128, 32, 8, 0), (64, 64, 8, 0), (96, 32, 8, 0),
+    (128, 128, 4, 1), (112, 96, 4, 1), (128, 64, 4, 0),    # two rounds
+    (112, 128, 6, 1), (96, 96, 8, 0), (128, 128, 16, 1),   # three and more
+])
+def test_coarsest_solve_of_many_right_hand_sides(exe, nx, ny, nb, want):
+    out = subprocess.run([exe], input=f"256 0 {nx} {ny} {nb}\n", check=True, capture_output=True, text=True).stdout
+    assert int(out) == want
