@@ -57,7 +57,8 @@ __device__ __forceinline__ void convp_issue_w(uint4* w, uint32_t wo, __amdgpu_bu
 #pragma unroll
   for (int i = 0; i < S::NW; ++i) {
     // threads per fragment column: S::NTHR / 64 fragments further on in the list of (step, tile)
-    const uint32_t off = (int)threadIdx.x + S::NTHR * i < n ? wo + i * (S::NTHR / 64 / ConvP<TN, TH>::MT) * 64 : 0x80000000u;
+    const uint32_t off =
+        (int)threadIdx.x + S::NTHR * i < n ? wo + i * (S::NTHR / 64 / ConvP<TN, TH>::MT) * 64 : 0x80000000u;
     w[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wr, (int)off, kbase * 2, 0));
   }
 }
@@ -192,7 +193,8 @@ __device__ __forceinline__ void convp_mfma_full(f32x4_t (&acc)[TN / 16][4], cons
       for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt)
-          acc[m][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[AHEAD ? tap & 1 : 0][m], b[nt + dy][dx], acc[m][nt], 0, 0, 0);
+          acc[m][nt] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[AHEAD ? tap & 1 : 0][m], b[nt + dy][dx], acc[m][nt], 0, 0, 0);
     }
   }
 }
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(TH * 16) __attribute__((amdgpu_waves_per_eu(TH == 1
 #pragma unroll
   for (int i = 0; i < S::NU; ++i) {
     const int p = (threadIdx.x >> 2) + S::PPR * i, ly = p / S::LW, lx = p - ly * S::LW;
- ln.yx[i] = (uint32_t)(ly | lx << 16);
+    ln.yx[i] = (uint32_t)(ly | lx << 16);
   }
   {
     const int f = threadIdx.x >> 6;
@@ -391,7 +393,8 @@ __global__ __launch_bounds__(TH * 16) __attribute__((amdgpu_waves_per_eu(TH == 1
     const int pyr = p.py0 + 4 * wv;
     if (p.k + 1 < nch || pyr >= g.H) return;
     if constexpr (OUTF)
-      conv_out_epilogue<MT, 4>(acc, g, s_b, pyr, p.px0 + (lane & 15), of, smp, [&](int m, int nt, int64_t) { return fpre[m][nt]; });
+      conv_out_epilogue<MT, 4>(acc, g, s_b, pyr, p.px0 + (lane & 15), of, smp,
+                               [&](int m, int nt, int64_t) { return fpre[m][nt]; });
     else
       conv_epilogue<TN, 4, false, false, false>(acc, g, s_b, co0, pyr, p.px0 + (lane & 15), s_t, yr, pr, of, smp, nbs, ksp,
                                                 ksplit, kpart);

@@ -486,8 +486,7 @@ __global__ __launch_bounds__(kMgCB) void k_mg_back(CoarseArgs a) {
   switch (R) {                                                   \
     case 2: { constexpr int RR = 2; __VA_ARGS__; } break;        \
     case 4: { constexpr int RR = 4; __VA_ARGS__; } break;        \
-    case 8: { constexpr int RR = 8; __VA_ARGS__; } break;        \
-    default: { constexpr int RR = 16; __VA_ARGS__; } break;      \
+    default: { constexpr int RR = 8; __VA_ARGS__; } break;       \
   }
 
 void launch_vcycle(const PcgArgs& pa, int nb, hipStream_t s) {

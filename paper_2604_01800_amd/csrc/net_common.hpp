@@ -66,8 +66,6 @@ __device__ __forceinline__ uint4 mul_bf16x8_s(uint4 v, uint32_t e16) {
 // laid out as the input), one per node (a [H][W] map).
 enum { kEtaNone = 0, kEtaChannel = 1, kEtaNode = 2 };
 
-constexpr int kConvTH = 8;   // conv pixel tile: 8 rows x 16 columns
-constexpr int kConvTW = 16;
 constexpr int kConvCK = 32;  // input channels staged per LDS chunk
 
 // Geometry of one MConv / conv layer as the kernels see it.

@@ -407,8 +407,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TN == 32 ? 
       conv_mfma<TN, TAPS, 0>(acc, s_x, s_w, ck8, lane, wv);
     if (c + 1 < c_lo + nch) continue;
 
-    conv_epilogue<TN, NT, UP, OUTF>(acc, g, s_b, co0, py0 + NT * wv, px0 + (lane & 15), s_t + wv * 512, yr, pr, of, smp, nbs, ksp, ksplit,
-                                    kpart);
+    conv_epilogue<TN, NT, UP, OUTF>(acc, g, s_b, co0, py0 + NT * wv, px0 + (lane & 15), s_t + wv * 512, yr, pr, of, smp,
+                                    nbs, ksp, ksplit, kpart);
   }
 }
 
@@ -998,7 +998,7 @@ static bool convp_fills(const ConvGeo& g, int64_t copies) {
 // source ends and the second source starts at a chunk; with 16, 24 or 40 channels at
 // the finest level some do not), offsets within a tile in 24-bit products.
 static bool convp_takes(const ConvGeo& g) {
-  return (!g.xu || g.cu % kConvCK == 0) && (!g.x1 || g.c1 % kConvCK == 0) && g.W <= (1 << 18) && 
+  return (!g.xu || g.cu % kConvCK == 0) && (!g.x1 || g.c1 % kConvCK == 0) && g.W <= (1 << 18) &&
          std::max({g.x_pitch, g.x1_pitch, g.xu_pitch, g.cin8}) < (1 << 22);
 }
 
@@ -1259,7 +1259,8 @@ bool plan_conv_group(int taps, bool up, int Kp, std::vector<ConvMember>& m, int6
       wgs64 += (int64_t)conv_tiles(e.g) * ((e.g.cout + 63) / 64);
       parts64.push_back(convp_part(e.g, (e.g.cout + 63) / 64));
     }
-    wide = wgs64 >= 2 * (int64_t)conv_device_cus() || (taps == 9 && !up && convp_runs(parts64, conv_device_cus()).fills);
+    wide = wgs64 >= 2 * (int64_t)conv_device_cus() ||
+           (taps == 9 && !up && convp_runs(parts64, conv_device_cus()).fills);
   }
   return conv_group_dispatch(taps, up, L.eta, wide, [&](auto tn, auto tp, auto upc, auto et) {
     conv_group_plan_t<decltype(tn)::value, decltype(tp)::value, decltype(upc)::value, decltype(et)::value>(

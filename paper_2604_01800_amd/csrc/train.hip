@@ -209,8 +209,8 @@ static ppe_status train_state(ppe_net* n, int nb, int nx, int ny) {
   t->dpart = (double*)dev_alloc(((size_t)kRedBlocks * (nb + 1) + 8) * sizeof(double));
   t->d_coefs = (Coef*)dev_alloc(nb * sizeof(Coef));
   t->d_masks = (const uint8_t**)dev_alloc(nb * sizeof(void*));
-  if (!t->act || !t->grad || (cfg.use_eta && !t->eta) || (cfg.use_eta == 2 && !t->se) || !t->packs || !t->f32 || !t->part || !t->rpart || !t->dpart ||
-      !t->d_coefs || !t->d_masks)
+  if (!t->act || !t->grad || (cfg.use_eta && !t->eta) || (cfg.use_eta == 2 && !t->se) || !t->packs || !t->f32 ||
+      !t->part || !t->rpart || !t->dpart || !t->d_coefs || !t->d_masks)
     return set_error(PPE_ERR_HIP, "allocation of the training workspace failed");
   HIPCHK(hipMemset(t->act, 0, ao * sizeof(bf16_t)));
   HIPCHK(hipMemset(t->grad, 0, go * sizeof(bf16_t)));

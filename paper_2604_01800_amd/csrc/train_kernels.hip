@@ -95,8 +95,8 @@ __global__ __launch_bounds__(64 * CT) __attribute__((amdgpu_waves_per_eu(2))) vo
     const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16_t*>(dp + smp * g.dp_bstride + pp * g.dp_pitch), (short)0, 0x7fffffff, 0x00020000);
     const __amdgpu_buffer_rsrc_t er = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(ETA != kEtaNone ? eta + smp * g.e_bstride + hp * (ETA == kEtaChannel ? g.cin8 : 1) : x), (short)0, 0x7fffffff,
-        0x00020000);
+        const_cast<bf16_t*>(ETA != kEtaNone ? eta + smp * g.e_bstride + hp * (ETA == kEtaChannel ? g.cin8 : 1) : x),
+        (short)0, 0x7fffffff, 0x00020000);
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
       const int u = tid + NT * i, px = u / GX, c = ci0 + (u - px * GX) * 8;
@@ -1594,7 +1594,10 @@ __global__ __launch_bounds__(256) void k_phi_grad(PhiArgs a) {
   float* row = a.part + (int64_t)blockIdx.x * len;
   for (int u = threadIdx.x; u < len; u += 256) {
     // u: W1 (q * 4 + k) | b1 (q) | W2 (q) | b2
-    const int k = u < a.hid * 4 ? u : u < a.hid * 5 ? HC * 4 + (u - a.hid * 4) : u < a.hid * 6 ? HC * 5 + (u - a.hid * 5) : HC * 6;
+    const int k = u < a.hid * 4   ? u
+                  : u < a.hid * 5 ? HC * 4 + (u - a.hid * 4)
+                  : u < a.hid * 6 ? HC * 5 + (u - a.hid * 5)
+                                  : HC * 6;
     float t = 0.f;
     for (int v = 0; v < kWaves; ++v) t += s_w[v][k];
     row[u] = t;
