@@ -1,10 +1,12 @@
 // Plain solves on grids of different sizes in one batch: every launch of the
 // two-step kernel (two iterations) or of the single-reduction kernel (one
 // iteration) runs over a work list of (solve, workgroup) entries, so small
-// grids ride along with large ones instead of leaving the GPU idle. Each solve keeps its own workspace, scalars, partial
-// sums and done flag; converged solves' workgroups exit at once. Chunks of
-// iterations are captured as one HIP graph and replayed until every flag is
-// set; the device records each solve's finishing time.
+// grids ride along with large ones instead of leaving the GPU idle. Each solve
+// keeps its own workspace, scalars, partial sums and done flag. A decided solve stays
+// in the list: its workgroups load their tiles and finish the partial sums of the last launch
+// before they see the flag, and write nothing. Chunks of iterations are captured
+// as one HIP graph and replayed until every flag is set; the device records each
+// solve's finishing time.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -1,5 +1,5 @@
-// The pipelined 3x3 convolution kernel and its launch, instantiated for 32 and for
-// 64 output channels per workgroup in a source file each.
+// The pipelined 3x3 convolution kernel and its launch, instantiated in a source file each
+// for 32 and 64 output channels per workgroup on tiles of 32 rows, and for 32 on tiles of 16.
 #pragma once
 #include <type_traits>
 
@@ -17,17 +17,19 @@ namespace ppe {
 // staged input is double buffered and one barrier separates items: a wavefront in turn
 // runs the MFMAs of an item, writes the next one to LDS, issues the loads of a later
 // one (two items in flight with 32 output channels and one chunk, layers that are bound
-// by memory, and with 16-row tiles) and stores its results; the second half of the wavefronts (the other one
-// on each SIMD) does this half a turn later, so that one's vector work runs beside the
-// other's MFMAs. Weights stay in LDS for the launch where all chunks fit (WRES), else
+// by memory, and with 16-row tiles) and stores its results; the second half of the
+// wavefronts (the other one on each SIMD) does this half a turn later, so that one's vector
+// work runs beside the other's MFMAs. Weights stay in LDS for the launch where all chunks fit (WRES), else
 // their slices are double buffered too.
 // LDS layouts: input pixels of 64 bytes, their 16-byte groups permuted by the
 // pixel number (eight consecutive pixels of one group lie in distinct banks);
 // weights as MFMA fragments, [step][16-channel tile][lane], read and written
 // without conflicts. In a full chunk a K-step is one tap, and the input rows
 // that two vertical taps share stay in registers: 18 input and 9 MT weight reads
-// for 36 MT MFMAs. The 3x3 layers of a 1024^2 forward took 689 us with k_conv and take
-// 534 us; the largest (104 channels to 32 at 1024^2) 135 -> 88 us, 0.71 PFLOP/s.
+// for 36 MT MFMAs. The 3x3 layers of a 1024^2 forward took 657 us with k_conv and take
+// 514 us; the largest (66 channels, 72 with padding, to 32 at 1024^2) 129 -> 84 us, 0.47
+// PFLOP/s and 3.2 TB/s. MFMA busy is 12-34 %; the wavefronts wait 30-47 % of their cycles at
+// barriers and for loads, mostly in the start of a launch.
 
 template <int TN, int TH>
 struct ConvP {

@@ -74,8 +74,10 @@ inline ConvpRuns convp_runs(const std::vector<ConvpPart>& parts, int64_t cus) {
   }
   ConvpRuns best;
   int64_t cost = 0;
+  const int64_t even = (tiles + cus - 1) / cus;
   const int64_t first = std::max<int64_t>(1, (images + cus - 1) / cus);  // one run per image needs these rounds
   for (int64_t k = first; k < first + 4; ++k) {
+    if (cost && cost <= even + 2) break;  // no unit with two workgroups has less
     int64_t run = std::min(longest, std::max<int64_t>(1, (tiles + k * cus - 1) / (k * cus)));
     // (steps of a thirty-second of the run: a grouped launch is planned on each call)
     for (;; run = std::min(longest, run + std::max<int64_t>(1, run / 32))) {
@@ -91,7 +93,7 @@ inline ConvpRuns convp_runs(const std::vector<ConvpPart>& parts, int64_t cus) {
       if (wgs <= k * cus || run == longest) break;
     }
   }
-  const int64_t even = (tiles + cus - 1) / cus, slots = cus * best.span;
+  const int64_t slots = cus * best.span;
   best.fills = 4 * tiles >= 3 * cus * even && (slots == cus || (3 * tiles >= 2 * slots && halves >= slots));
   return best;
 }

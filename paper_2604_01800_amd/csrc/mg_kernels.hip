@@ -18,7 +18,7 @@
 // A level costs two launches: down (pre-smoothing, residual, restriction) and
 // up (prolongation, both post steps). Each takes two stencil applications on a
 // tile with a two-cell halo, recomputed instead of exchanged: the cycle is bound by the
-// latency of its dependent launches (2.6 to 5 us each at 128^2 to 1024^2, for
+// latency of its dependent launches (3.2 to 6.3 us each at 256^2 to 1024^2, for
 // at most 4 MB a vector), not by the bytes or the arithmetic that the wider halo adds. A
 // kernel that reads a vector on a halo never writes that vector (other
 // workgroups may still be reading it): x2 lives in x, x5 in y. The coarsest
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_cbwd(CoarseArgs a) {
 // rows [32 part, 32 part + 32) of each transform's column j in registers, the
 // four parts of a sum meet in LDS, and only LDS traffic is left between the
 // transforms. The three launches waited on the L2 four times per transform
-// with half of their threads idle: 19.1 us at 128 x 128, against 8.1 + 6.0 us here.
+// with half of their threads idle: 19.1 us at 128 x 128, against 7.7 + 6.0 us here.
 // (On FP64 matrix cores, 16 modes per workgroup, the same work took 39 us: eight
 // compute units then load all of the matrices.)
 //

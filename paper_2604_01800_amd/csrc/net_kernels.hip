@@ -1115,6 +1115,7 @@ static void conv_group_plan_t(std::vector<ConvMember>& m, int64_t kpart_elems, C
   const int nch = (g0.cin8 + ConvShape<TN, TAPS>::CK - 1) / ConvShape<TN, TAPS>::CK;
   int64_t wgs = 0, kwg = 0;
   std::vector<ConvpPart> parts;
+  parts.reserve(m.size());
   bool wstat = true, takes = TAPS == 9 && !UP;
   for (ConvMember& e : m) {
     // the K split of the member's own launch (its own tile width)
@@ -1255,6 +1256,7 @@ bool plan_conv_group(int taps, bool up, int Kp, std::vector<ConvMember>& m, int6
   if (m[0].g.cout >= 64) {
     int64_t wgs64 = 0;
     std::vector<ConvpPart> parts64;
+    parts64.reserve(m.size());
     for (const ConvMember& e : m) {
       wgs64 += (int64_t)conv_tiles(e.g) * ((e.g.cout + 63) / 64);
       parts64.push_back(convp_part(e.g, (e.g.cout + 63) / 64));

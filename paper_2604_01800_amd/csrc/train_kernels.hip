@@ -303,9 +303,11 @@ __global__ __launch_bounds__(256) void k_wgrad1(WgradGeo g, const bf16_t* __rest
 // as they are and the weights from LDS (wave w the pixels 16 w ..); its result
 // replaces d in LDS and leaves as whole 16-byte pieces. The next stage's loads are in flight
 // meanwhile.
-// Bound by HBM: 768 B per pixel at 128 channels (d and x read, dx written) where
-// separate launches for dW, dx and act' moved 1.8 KB. At 4.2 M pixels a
-// 128 x 128 layer takes 870 us against 286 + 385 + 420.
+// 768 B per pixel at 128 channels (d and x read, dx written) where separate launches for
+// dW, dx and act' moved 1.8 KB. At 4.2 M pixels a 128 x 128 layer takes 766 us
+// (4.3 TB/s; a large copy reaches 5.1) against 286 + 385 + 420. Bound by the barriers of
+// a stage (four, 64 pixels apart) and its loads: the wavefronts wait about half of their
+// cycles, MFMA busy is 15 %. The bias gradient is a launch of its own (k_bias_grad).
 constexpr int kB1P = 64;     // pixels per stage
 constexpr int kB1C = 128;    // channels at most
 constexpr int kB1DP = kB1C + 16;  // LDS pitch (bf16) of a pixel: see k_wgrad9
