@@ -13,7 +13,7 @@ namespace ppe {
 // those with at most one 16 x 16 tile per compute unit (TH = 16, four wavefronts, also
 // with a split K), which only ever wait for their own loads. What
 // bounded k_conv was the wait for an item's loads between two barriers, the vector
-// work beside the MFMAs (MFMA busy 12-28 %) and its stores of 8 bytes a lane. Here the
+// work beside the MFMAs (MFMA busy 6-25 %) and its stores of 8 bytes a lane. Here the
 // staged input is double buffered and one barrier separates items: a wavefront in turn
 // runs the MFMAs of an item, writes the next one to LDS, issues the loads of a later
 // one (two items in flight with 32 output channels and one chunk, layers that are bound
@@ -28,7 +28,7 @@ namespace ppe {
 // that two vertical taps share stay in registers: 18 input and 9 MT weight reads
 // for 36 MT MFMAs. The 3x3 layers of a 1024^2 forward took 657 us with k_conv and take
 // 514 us; the largest (66 channels, 72 with padding, to 32 at 1024^2) 129 -> 84 us, 0.47
-// PFLOP/s and 3.2 TB/s. MFMA busy is 12-34 %; the wavefronts wait 30-47 % of their cycles at
+// PFLOP/s and 3.2 TB/s. MFMA busy is 7-34 %; the wavefronts wait 30-61 % of their cycles at
 // barriers and for loads, mostly in the start of a launch.
 
 template <int TN, int TH>
