@@ -40,7 +40,7 @@ def test_vcycle_at_tile_edges(nx, ny, levels, nb):
 
 @pytest.mark.parametrize("nx,ny,levels,nb", [
     (64, 64, 4, 32), (64, 64, 4, 33),    # 256 and 264 workgroups of the first coarse launch: two and three launches
-    (256, 140, 2, 4), (256, 128, 2, 3),  # two rounds of them, with 70 and with 64 rows: two and three launches
+    (132, 132, 2, 4), (128, 132, 2, 5),  # two rounds of them, axes of 66 and of 64 cells: two and three launches
 ])
 def test_vcycle_of_many_right_hand_sides(nx, ny, levels, nb):
     from paper_2604_01800_amd import ppe
